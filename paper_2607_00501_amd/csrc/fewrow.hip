@@ -1,0 +1,89 @@
+// Dense launches of the few-row matmul kernel (fewrow.h): any format, one
+// matrix or a group.
+#include <cstdio>
+
+#include "fewrow.h"
+
+namespace qm {
+namespace {
+
+template <int FMT, int RT, int XR, int U>
+hipError_t launch_tile(const QgemmArgs& a, hipStream_t st) {
+  const int64_t subs = static_cast<int64_t>(a.gpanel[a.gcount]) * (4 / RT);
+  const dim3 grid(static_cast<unsigned>(subs), static_cast<unsigned>((a.M + 4 * XR - 1) / (4 * XR)));
+  hipLaunchKernelGGL((fewrow_kernel<FMT, RT, XR, U, QgMode::kDense>), grid, dim3(fr::kWaves * 64), 0, st, a);
+  return hipGetLastError();
+}
+
+// The tiles fewrow_plan() can choose, in its order of preference.  RT <= 2
+// tiles exist with one and two steps in flight.
+#define QM_FEWROW_TILES(X) X(1, 2) X(1, 4) X(2, 2) X(2, 4) X(4, 2) X(4, 4) X(4, 8)
+
+template <int FMT>
+hipError_t launch_fmt(const QgemmArgs& a, const FewrowPlan& f, hipStream_t st) {
+#define QM_FR(RT, XR) \
+  if (f.rt == RT && f.xr == XR) \
+    return RT <= 2 && f.u == 2 ? launch_tile<FMT, RT, XR, RT <= 2 ? 2 : 1>(a, st) : launch_tile<FMT, RT, XR, 1>(a, st);
+  QM_FEWROW_TILES(QM_FR)
+#undef QM_FR
+  return hipErrorInvalidConfiguration;
+}
+
+}  // namespace
+
+// The first tile of the list whose grid fits one workgroup per CU: more rows
+// per workgroup mean fewer reads of the activations and of the weights, fewer
+// workgroups idle CUs.  Measured on MI355X (256 CUs, weights from HBM, us per
+// call, old: the tiles of gemm_plan):
+//   Q4 3072 -> 2 x 8192: m = 8 14.4 -> 8.2, 16 14.9 -> 8.7, 32 15.3 -> 11.3
+//   (256 panels: RT = 4; RT = 2 takes 8.9 / 10.4 / 13.7);
+//   Q4 2048 -> 3072 wide: m = 8 7.3 -> 4.1, 32 7.7 -> 5.0, 77 7.9 -> 5.7
+//   (RT = 1 / 2 / 4; two rounds of a smaller tile take 4.6 / 5.6 / 6.5);
+//   Q4 8192 -> 3072: m = 8 17.4 -> 7.8, 64 18.8 -> 14.3.
+// Where it loses, from a sweep over all formats: RT = 4 with fewer than 3/4
+// workgroup per CU (dequantisation is the bound there and CUs idle; Q8 at
+// m = 17, n = 4785: 12.5 vs 14.0), beyond 128 rows (Q4 1344 -> 1577 at m = 307:
+// 7.9 vs 8.6), XR = 8 at long K (Q4 8192 -> 3072 at m = 128: 17.3 vs 18.1) and
+// for Q8, F16 and BF16, whose weight registers are twice as many or more (F16
+// 2048 -> 3072 at m = 64: 8.0 vs 8.8).  Matrices with more panels than CUs take
+// whole panels up to 32 rows.  Two steps in flight help from K = 4096 (8192 ->
+// 3072 at m = 8: 9.2 -> 7.8) and cost up to 6% at K = 1024.
+FewrowPlan fewrow_plan(int32_t fmt, int64_t m, int64_t n, int64_t k, int cu_count) {
+  // Tuning sweeps only: QM_FEWROW_PLAN="rt,xr,u" forces the plan (rt = 0: none).
+  if (const char* e = tuning_override("QM_FEWROW_PLAN")) {
+    FewrowPlan f{0, 0, 1};
+    std::sscanf(e, "%d,%d,%d", &f.rt, &f.xr, &f.u);
+    return f;
+  }
+  const int64_t panels = padded_rows(n) / kPanel;
+  const bool wide = fmt_bits(fmt) >= 8;
+  auto take = [&](int rt, int xr) {
+    const int64_t groups = panels * (4 / rt) * ((m + 4 * xr - 1) / (4 * xr));
+    if (groups > cu_count) return false;
+    if (rt < 4 || m <= 16 || (m <= 32 && !wide)) return true;
+    if (m > 128 || 4 * groups < 3 * cu_count) return false;
+    return m <= 32 || (!fmt_float(fmt) && (xr < 8 || (!wide && k <= 4096)));
+  };
+#define QM_FR(RT, XR) \
+  if (take(RT, XR)) return FewrowPlan{RT, XR, RT <= 2 && k >= 4096 ? 2 : 1};
+  QM_FEWROW_TILES(QM_FR)
+#undef QM_FR
+  if (m <= 32 && panels > cu_count) return FewrowPlan{4, m <= 8 ? 2 : m <= 16 ? 4 : 8, 1};
+  return FewrowPlan{0, 0, 1};
+}
+
+hipError_t launch_fewrow(const QgemmArgs& a, int32_t fmt, const FewrowPlan& f, hipStream_t st) {
+  switch (fmt) {
+    case QM_Q4_G32: return launch_fmt<QM_Q4_G32>(a, f, st);
+    case QM_Q8_G32: return launch_fmt<QM_Q8_G32>(a, f, st);
+    case QM_Q2_G32: return launch_fmt<QM_Q2_G32>(a, f, st);
+    case QM_Q3_G32: return launch_fmt<QM_Q3_G32>(a, f, st);
+    case QM_Q5_G32: return launch_fmt<QM_Q5_G32>(a, f, st);
+    case QM_Q6_G32: return launch_fmt<QM_Q6_G32>(a, f, st);
+    case QM_F16: return launch_fmt<QM_F16>(a, f, st);
+    case QM_BF16: return launch_fmt<QM_BF16>(a, f, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace qm

@@ -84,6 +84,8 @@ namespace {
 hipError_t launch_args(const QgemmArgs& a, int32_t fmt, int cu_count, hipStream_t st) {
   const int64_t panels = a.gpanel[a.gcount];
   if (panels == 0) return hipSuccess;
+  const FewrowPlan fp = fewrow_plan(fmt, a.M, panels * kPanel, a.K, cu_count);
+  if (fp.rt != 0) return launch_fewrow(a, fmt, fp, st);
   const GemmPlan p = gemm_plan(a.M, panels * kPanel, a.K, cu_count);
 #define QM_LAUNCH_FMT(F) \
   if (fmt == F) {                                                                            \

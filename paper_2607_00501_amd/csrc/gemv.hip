@@ -23,6 +23,7 @@
 //    position, F16 feeds the stored pairs to v_dot2_f32_f16 and BF16 (the
 //    upper half of an fp32) goes through fp32 fma with the fp16 activation
 //    (Sec. 4.1: eight formats, one kernel each).
+#include "chunk.h"
 #include "qm_internal.h"
 #include "rope.h"
 
@@ -60,9 +61,6 @@ template <int FMT> constexpr int kPanelUnroll = FMT == QM_Q4_G32 ? 8 : FMT == QM
                                               : FMT == QM_Q5_G32 ? 6 : FMT == QM_Q6_G32 ? 5 : 2;
 // Words (dwords) of one lane's chunk: 32 codes of b bits = b dwords.
 template <int FMT> constexpr int kWords = fmt_bits(FMT);
-
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 // In the large-matrix kernel weights and scales are streamed once per call:
 // nontemporal loads raise the sustained read rate (measured +12% on a plain
@@ -334,44 +332,6 @@ __device__ __forceinline__ float dot_chunk(const uint32_t* d, const uint32_t* xs
   else if constexpr (FMT == QM_Q2_G32 || FMT == QM_Q3_G32) return dot_crumb<FMT>(d, xs, k);
   else if constexpr (FMT == QM_F16) return dot_f16(d, xs);
   else return dot_bf16(d, xs);
-}
-
-// One lane's share of chunk block `blk` (panel row r): the planes, halves or
-// quarters of the device layout, each a coalesced wavefront load.
-template <int W, bool NT>
-__device__ __forceinline__ void load_words(const uint8_t* p, uint32_t* d) {
-  if constexpr (W == 4) {
-    const u32x4 v = NT ? __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)) : *reinterpret_cast<const u32x4*>(p);
-    d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
-  } else if constexpr (W == 2) {
-    const u32x2 v = NT ? __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p)) : *reinterpret_cast<const u32x2*>(p);
-    d[0] = v.x; d[1] = v.y;
-  } else {
-    d[0] = NT ? __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(p)) : *reinterpret_cast<const uint32_t*>(p);
-  }
-}
-template <int FMT, bool NT>
-__device__ __forceinline__ void load_chunk(const uint8_t* blk, int r, uint32_t* d) {
-  if constexpr (FMT == QM_Q4_G32) {
-    load_words<4, NT>(blk + 16 * r, d);
-  } else if constexpr (FMT == QM_Q8_G32) {
-    load_words<4, NT>(blk + 16 * r, d);
-    load_words<4, NT>(blk + 1024 + 16 * r, d + 4);
-  } else if constexpr (FMT == QM_Q2_G32) {
-    load_words<2, NT>(blk + 8 * r, d);
-  } else if constexpr (FMT == QM_Q3_G32) {
-    load_words<2, NT>(blk + 8 * r, d);
-    load_words<1, NT>(blk + 512 + 4 * r, d + 2);
-  } else if constexpr (FMT == QM_Q5_G32) {
-    load_words<4, NT>(blk + 16 * r, d);
-    load_words<1, NT>(blk + 1024 + 4 * r, d + 4);
-  } else if constexpr (FMT == QM_Q6_G32) {
-    load_words<4, NT>(blk + 16 * r, d);
-    load_words<2, NT>(blk + 1024 + 8 * r, d + 4);
-  } else {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) load_words<4, NT>(blk + 1024 * j + 16 * r, d + 4 * j);
-  }
 }
 
 // Group sum -> contribution: times the fp16 group scale (integer formats).

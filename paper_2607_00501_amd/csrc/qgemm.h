@@ -51,6 +51,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "chunk.h"
 #include "qm_internal.h"
 
 namespace qm {
@@ -83,10 +84,10 @@ struct QgemmArgs {
   int64_t gn[kGemmGroupMax];
 };
 
-namespace qg {
+// Dense launch of the few-row kernel (fewrow.h).
+hipError_t launch_fewrow(const QgemmArgs& a, int32_t fmt, const FewrowPlan& f, hipStream_t st);
 
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+namespace qg {
 
 constexpr int kBK = 64;                 // K per step (two quantisation groups)
 constexpr int kMoeChunkTiles = 4;       // MoE row tiles per XCD chunk

@@ -250,6 +250,10 @@ void gemv_kernel_name(int32_t fmt, int64_t n, int64_t k, int cu_count, char* buf
 struct GemmPlan { int bm; int wn; int wk; };   // rows per tile, panels (wavefronts) per K slice, K slices
 GemmPlan gemm_plan(int64_t m, int64_t n, int64_t k, int cu_count);
 bool gemm_plan_instantiated(const GemmPlan& p);   // a prefill GEMM tile exists for p
+// Few-row launch plan: rt 16-row weight tiles and 4 xr activation rows per
+// workgroup, u steps in flight (rt = 0: take the tiles of gemm_plan).
+struct FewrowPlan { int rt; int xr; int u; };
+FewrowPlan fewrow_plan(int32_t fmt, int64_t m, int64_t n, int64_t k, int cu_count);
 const char* gemm_tile_name(int64_t m, int64_t n);
 const char* moe_tile_name(int64_t rows_per_expert);
 
