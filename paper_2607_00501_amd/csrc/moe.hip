@@ -17,7 +17,7 @@
 #include <mutex>
 #include <utility>
 
-#include "qgemm.h"
+#include "fewrow.h"
 
 namespace qm {
 namespace {
@@ -254,6 +254,124 @@ __global__ __launch_bounds__(kBucketThreads) void bucket_kernel(const int32_t* _
   }
 }
 
+// ------------------------------------------- routing of a decode batch
+
+// A few tokens (m rounded-up E <= 2048 logits, m top_k <= 128 assignments):
+// routing and bucketing in one workgroup and one launch.  Both kernels above
+// are chains of dependent steps (top_k wavefront argmaxes; counts, scan,
+// ballots) on a few wavefronts; here every order statistic is a count, taken
+// in parallel by the 1024 threads: the slot of an expert is the number of
+// experts that go before it, the place of an assignment the number of
+// assignments that go before it, an expert's offset the number of assignments
+// to lower experts.  128 experts, top-8: 10.4 -> 4.2 us at one token, 11.0 ->
+// 8.6 at 8; 64 experts, top-6: 9.7 -> 7.7 at 16.
+constexpr int kSmallRouteLogits = 2048;
+constexpr int kSmallRouteAssign = 128;
+__host__ __device__ constexpr int small_route_log_stride(int E) { return E <= 64 ? 6 : E <= 128 ? 7 : 8; }
+// The compares are m E^2; about 10 tokens of 128 experts is where the two
+// launches above catch up.
+inline bool small_route(int64_t m, int32_t e, int32_t k) {
+  const int64_t s = 1 << small_route_log_stride(e);
+  return m > 0 && e <= 256 && m * s <= kSmallRouteLogits && m * s * s <= 10 * 128 * 128 && m * k <= kSmallRouteAssign;
+}
+
+// Floats as integers of the same order, -0 as +0, NaN as 1 (below every
+// number) and above the padding's 0.
+__device__ __forceinline__ uint32_t order_key(float v) {
+  if (v != v) return 1u;
+  const uint32_t b = __builtin_bit_cast(uint32_t, v + 0.0f);
+  return b & 0x80000000u ? ~b : b | 0x80000000u;
+}
+__device__ __forceinline__ float order_value(uint32_t k) {
+  if (k == 1u) return __builtin_nanf("");
+  return __builtin_bit_cast(float, k & 0x80000000u ? k & 0x7FFFFFFFu : ~k);
+}
+
+__global__ __launch_bounds__(1024) void route_small_kernel(const float* __restrict__ logits, int m, int E, int K,
+                                                           int32_t* __restrict__ ids, float* __restrict__ gates,
+                                                           int32_t* __restrict__ counts,
+                                                           int32_t* __restrict__ offsets,
+                                                           int32_t* __restrict__ sorted_assign) {
+  __shared__ __attribute__((aligned(16))) uint32_t key[kSmallRouteLogits];      // rows of 2^ls, padded with 0
+  __shared__ __attribute__((aligned(16))) int32_t sel_id[kSmallRouteAssign];    // padded with INT32_MAX
+  __shared__ float sel_v[kSmallRouteAssign];
+  const int tid = threadIdx.x;
+  const int ls = small_route_log_stride(E), S = 1 << ls, A = m * K;
+  for (int i = tid; i < m << ls; i += 1024) {
+    const int t = i >> ls, e = i & (S - 1);
+    key[i] = e < E ? order_key(logits[t * E + e]) : 0u;
+  }
+  if (tid < kSmallRouteAssign) sel_id[tid] = 0x7FFFFFFF;
+  __syncthreads();
+  // Slot of expert e among its token's: 2^lp threads a pair, each over a share
+  // of the experts, four at a time.  An equal logit goes first if its index is
+  // lower: below e's own four the test is key > ke - 1, from there on
+  // key > ke, and equals inside the four are added at the end.
+  int lp = 0;
+  while (lp < 4 && m << (ls + lp + 1) <= 1024) ++lp;
+  for (int it = tid; it < m << (ls + lp); it += 1024) {   // 64-lane groups stay whole
+    const int pair = it >> lp, part = it & ((1 << lp) - 1);
+    const int t = pair >> ls, e = pair & (S - 1);
+    const uint4* row = reinterpret_cast<const uint4*>(key + (t << ls));
+    const uint32_t ke = key[pair];
+    const int e4 = e >> 2;
+    int rank = 0;
+#pragma unroll 4
+    for (int o = part; o < S / 4; o += 1 << lp) {
+      const uint4 ko = row[o];
+      const uint32_t kk = o < e4 ? ke - 1u : ke;          // (padding: ke = 0, its rank is not used)
+      rank += (ko.x > kk) + (ko.y > kk) + (ko.z > kk) + (ko.w > kk);
+    }
+    for (int off = 1; off < 1 << lp; off <<= 1) rank += __shfl_xor(rank, off);
+    const uint4 own = row[e4];
+    rank += ((e & 3) > 0 && own.x == ke) + ((e & 3) > 1 && own.y == ke) + ((e & 3) > 2 && own.z == ke);
+    if (part == 0 && e < E && rank < K) {
+      sel_id[t * K + rank] = e;
+      sel_v[t * K + rank] = order_value(ke);
+    }
+  }
+  __syncthreads();
+  const int4* id4 = reinterpret_cast<const int4*>(sel_id);
+  if (tid < E) {
+    // Expert tid: its assignments and those of lower experts.
+    int c = 0, lower = 0;
+    for (int b = 0; b < A; b += 4) {
+      const int4 v = id4[b / 4];
+      c += (v.x == tid) + (v.y == tid) + (v.z == tid) + (v.w == tid);
+      lower += (v.x < tid) + (v.y < tid) + (v.z < tid) + (v.w < tid);
+    }
+    counts[tid] = c;
+    offsets[tid] = lower;
+    if (tid == 0) offsets[E] = A;
+  }
+  const int a = tid - 512;                                // other wavefronts: assignment a
+  if (a >= 0 && a < A) {
+    const int id = sel_id[a];
+    int pos = 0;
+    for (int b = 0; b < A; b += 4) {
+      const int4 v = id4[b / 4];
+      pos += v.x < id || (v.x == id && b < a) ? 1 : 0;
+      pos += v.y < id || (v.y == id && b + 1 < a) ? 1 : 0;
+      pos += v.z < id || (v.z == id && b + 2 < a) ? 1 : 0;
+      pos += v.w < id || (v.w == id && b + 3 < a) ? 1 : 0;
+    }
+    sorted_assign[pos] = a;
+    // Softmax over the token's selected logits relative to the largest, the
+    // denominator in the pairwise order of route_kernel's butterfly.
+    const int s0 = a / K * K;
+    const float vmax = sel_v[s0];
+    float ex[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) ex[j] = j < K ? expf(sel_v[s0 + min(j, K - 1)] - vmax) : 0.0f;
+#pragma unroll
+    for (int w = 1; w < 16; w <<= 1)
+#pragma unroll
+      for (int j = 0; j < 16; j += 2 * w) ex[j] += ex[j + w];
+    ids[a] = id;
+    gates[a] = expf(sel_v[a] - vmax) / ex[0];
+  }
+}
+
 // ---------------------------------------------------------------- combine
 
 // y[t][n] = sum over slots j (in order) of the gate-weighted expert outputs
@@ -282,6 +400,13 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint16_t* __restrict
   float4* dst = reinterpret_cast<float4*>(y + t * hidden) + 2 * c;
   dst[0] = make_float4(s[0], s[1], s[2], s[3]);
   dst[1] = make_float4(s[4], s[5], s[6], s[7]);
+}
+
+hipError_t launch_combine(const MoeArgs& a, hipStream_t st) {
+  const int64_t n8 = a.m * (a.hidden / 8);
+  hipLaunchKernelGGL(combine_kernel, dim3(static_cast<unsigned>((n8 + 255) / 256)), dim3(256), 0, st, a.yp,
+                     a.y, a.m, a.hidden, a.top_k);
+  return hipGetLastError();
 }
 
 template <int BMG, int WKG, int BMD, int WKD, int WN, int DG = 2, int DD = 2, bool NT = false, int FMT = QM_Q4_G32>
@@ -316,10 +441,36 @@ hipError_t launch_moe_tiles(const MoeArgs& a, hipStream_t st) {
                      st, g);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int64_t n8 = a.m * (a.hidden / 8);
-  hipLaunchKernelGGL(combine_kernel, dim3(static_cast<unsigned>((n8 + 255) / 256)), dim3(256), 0, st, a.yp,
-                     a.y, a.m, a.hidden, a.top_k);
-  return hipGetLastError();
+  return launch_combine(a, st);
+}
+
+// The two grouped products on the few-row kernel: RTG / RTD 16-row weight tiles
+// and 4 XR bucket rows per workgroup.
+template <int RTG, int RTD, int XR, int FMT>
+hipError_t launch_moe_fewrow(const MoeArgs& a, hipStream_t st) {
+  const int64_t A = a.m * a.top_k;
+  QgemmArgs g{};
+  g.counts = a.counts; g.offsets = a.offsets; g.sorted_assign = a.sorted_assign; g.topk_w = a.topk_w;
+  g.topk_ids = a.topk_ids;
+  g.n_experts = a.n_experts; g.top_k = a.top_k; g.M = A;
+  // At most one (expert, row block) pair per assignment.
+  g.tiles = std::min<int64_t>(A, (A + 4 * XR - 1) / (4 * XR) + a.n_experts);
+  auto grid = [&](int rt, int64_t n) {
+    const int64_t sp = 4 / rt, round = kXcds * sp;
+    const int64_t units = g.tiles * (padded_rows(n) / kPanel) * sp;
+    return dim3(static_cast<unsigned>((units + round - 1) / round * round));
+  };
+  g.q = a.gq; g.s = a.gs; g.q2 = a.uq; g.s2 = a.us; g.a = a.x; g.h = a.h; g.N = a.inter; g.K = a.hidden;
+  hipLaunchKernelGGL((fewrow_kernel<FMT, RTG, XR, 1, QgMode::kMoeGateUp>), grid(RTG, a.inter), dim3(fr::kWaves * 64),
+                     0, st, g);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  g.q = a.dq; g.s = a.ds; g.q2 = nullptr; g.s2 = nullptr; g.a = a.h; g.yp = a.yp; g.N = a.hidden; g.K = a.inter;
+  hipLaunchKernelGGL((fewrow_kernel<FMT, RTD, XR, 1, QgMode::kMoeDown>), grid(RTD, a.hidden), dim3(fr::kWaves * 64),
+                     0, st, g);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return launch_combine(a, st);
 }
 
 }  // namespace
@@ -368,6 +519,11 @@ const char* moe_tile_name(int64_t rows_per_expert) {
 
 hipError_t launch_route(const float* logits, int64_t m, int32_t e, int32_t k, int32_t* ids, float* w,
                         int32_t* counts, int32_t* offsets, int32_t* sorted_assign, hipStream_t st) {
+  if (small_route(m, e, k)) {
+    hipLaunchKernelGGL(route_small_kernel, dim3(1), dim3(1024), 0, st, logits, static_cast<int>(m), e, k, ids, w,
+                       counts, offsets, sorted_assign);
+    return hipGetLastError();
+  }
   if (m > 0) {
     const unsigned blocks = static_cast<unsigned>((m + 3) / 4);
     const dim3 g(blocks), b(kRouteThreads);
@@ -414,9 +570,18 @@ hipError_t launch_moe(const MoeArgs& a, int cu_count, hipStream_t st) {
   // (their LDS stages do not fit beside two workgroups' A stages), and the
   // two-matrix gate/up tile then holds 64 rows only by spilling: their
   // gate/up tiles stay at 32 rows.
+  // At most 1.5 rows per expert in the mean (decode batches): the few-row
+  // kernel with 32-row sub-panels for gate/up, whole panels for down and 8-row
+  // blocks; the 32 x 256 tiles leave 24 workgroups busy at one token.
+  // Measured on MI355X (128 experts, top-8, 2048 -> 768 -> 2048, Q4, us for the
+  // three launches): 45.9 -> 18.3 at 1 token, 46.8 -> 32.0 at 4, 77.1 -> 61.8 at
+  // 16, 86.7 -> 80.0 at 32, 90.8 -> 93.0 at 64; Q3 and Q5 turn at 1.5 rows per
+  // expert (Q3 95.8 -> 89.2 at 1, 103.8 -> 113.5 at 2).
   const int64_t rpe = a.m * a.top_k / a.n_experts;
+  const bool few = 2 * a.m * a.top_k <= 3 * static_cast<int64_t>(a.n_experts);
   auto plan = [&](auto f) -> hipError_t {
     constexpr int F = decltype(f)::value;
+    if (few) return launch_moe_fewrow<2, 4, 2, F>(a, st);
     if (rpe <= 24) return launch_moe_tiles<32, 1, 32, 1, 4, 2, 2, true, F>(a, st);
     if constexpr (F == QM_Q5_G32 || F == QM_Q6_G32 || F == QM_Q8_G32) {
       return launch_moe_tiles<32, 1, 64, 1, 4, 2, 2, false, F>(a, st);
