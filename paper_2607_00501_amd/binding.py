@@ -26,7 +26,7 @@ LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libqmatmul.
 
 EXPORTS = ("qm_last_error", "qm_weight_bytes", "qm_quantise", "qm_dequantise", "qm_repack",
            "qmatmul_gemv", "qmatmul_gemv_swiglu", "qmatmul_gemv_grouped", "qmatmul_gemm",
-           "qmatmul_gemm_grouped",
+           "qmatmul_gemm_grouped", "qmatmul_gemm_swiglu_f16",
            "qmoe_workspace_bytes", "qmoe_route",
            "qmoe_grouped_gemm", "qmoe_grouped_gemm_noalloc", "qm_device_config", "qattn_decode_workspace_bytes", "qattn_decode",
            "qattn_prefill", "qdec_embed", "qdec_rmsnorm", "qdec_rope_append", "qdec_cast_f16",
@@ -72,6 +72,7 @@ def lib() -> ctypes.CDLL:
             "qmatmul_gemv_grouped": [i32, W, ctypes.POINTER(vp), ctypes.POINTER(vp), vp],
             "qmatmul_gemm": [W, vp, i64, vp, vp],
             "qmatmul_gemm_grouped": [i32, W, vp, i64, ctypes.POINTER(vp), vp],
+            "qmatmul_gemm_swiglu_f16": [W, W, vp, i64, vp, vp],
             "qmoe_workspace_bytes": [i64, i32, i32, i64, i64, ctypes.POINTER(sz)],
             "qmoe_route": [vp, i64, i32, i32, vp, vp, vp, vp, vp, vp],
             "qmoe_grouped_gemm": [W, W, W, vp, i64, i32, vp, vp, vp, vp, vp, vp, vp, sz, vp],
@@ -417,6 +418,19 @@ def qmatmul_gemm_grouped(ws, x: torch.Tensor, outs=None, stream=None):
     n, descs, yp = gemm_group_args(ws, outs)
     _check(lib().qmatmul_gemm_grouped(n, descs, _ptr(x), m, yp, _stream(stream)))
     return outs
+
+
+def qmatmul_gemm_swiglu_f16(w_gate: QWeight, w_up: QWeight, x: torch.Tensor, out: Optional[torch.Tensor] = None,
+                            stream=None):
+    """X: fp16 [m][k] -> fp16(silu(X Wg'^T) * (X Wu'^T)), [m][n]."""
+    assert x.dtype == torch.float16 and x.is_contiguous() and x.dim() == 2 and x.shape[1] == w_gate.k
+    m = x.shape[0]
+    if out is None:
+        out = torch.empty((m, w_gate.n), dtype=torch.float16, device=x.device)
+    assert out.dtype == torch.float16 and out.is_contiguous() and out.numel() == m * w_gate.n
+    _check(lib().qmatmul_gemm_swiglu_f16(ctypes.byref(w_gate.c()), ctypes.byref(w_up.c()), _ptr(x), m, _ptr(out),
+                                         _stream(stream)))
+    return out
 
 
 def qattn_decode_workspace_bytes(n_q_heads: int, head_dim: int) -> int:

@@ -520,6 +520,38 @@ qm_status qmatmul_gemm_grouped(int32_t count, const qm_qweight* w, const uint16_
                   "qmatmul_gemm_grouped");
 }
 
+qm_status qmatmul_gemm_swiglu_f16(const qm_qweight* w_gate, const qm_qweight* w_up, const uint16_t* x, int64_t m,
+                                  uint16_t* h, void* stream) {
+  const char* name = "qmatmul_gemm_swiglu_f16";
+  const qm_qweight* ws[2] = {w_gate, w_up};
+  for (const qm_qweight* w : ws) {
+    qm_status st = check_weight(w, name);
+    if (st != QM_OK) return st;
+    if (w->layout != QM_LAYOUT_DEVICE) return fail(QM_ELAYOUT, "%s: weights must be in DEVICE layout", name);
+    if (w->batch != 1) return fail(QM_ESHAPE, "%s: batch must be 1", name);
+  }
+  if (w_up->format != w_gate->format) return fail(QM_EFORMAT, "%s: gate and up formats differ", name);
+  if (w_up->n != w_gate->n || w_up->k != w_gate->k) return fail(QM_ESHAPE, "%s: gate and up shapes differ", name);
+  if (w_gate->n > (int64_t(1) << 29)) return fail(QM_ESHAPE, "%s: too many rows", name);
+  if (m < 1 || m > 65536) return fail(QM_ESHAPE, "%s: m=%lld must be in [1, 65536]", name, (long long)m);
+  if (w_gate->n > 0 && (!x || !h)) return fail(QM_EINVAL, "%s: null x or h", name);
+  if (!aligned16(x)) return fail(QM_EALIGN, "%s: x must be 16-byte aligned", name);
+  if (!aligned2(h)) return fail(QM_EALIGN, "%s: h must be 2-byte aligned", name);
+  const DeviceInfo* d;
+  qm_status st;
+  if ((st = device_info(&d)) != QM_OK) return st;
+  const hipStream_t s = static_cast<hipStream_t>(stream);
+  const uint8_t* qg = static_cast<const uint8_t*>(w_gate->qdata);
+  const uint8_t* qu = static_cast<const uint8_t*>(w_up->qdata);
+  if (m == 1)
+    return launched(launch_gemv_swiglu(w_gate->format, qg, w_gate->scales, qu, w_up->scales, x, nullptr, h, w_gate->n,
+                                       w_gate->k, d->cu_count, s),
+                    name);
+  return launched(launch_gemm_swiglu(w_gate->format, qg, w_gate->scales, qu, w_up->scales, x, h, m, w_gate->n,
+                                     w_gate->k, d->cu_count, s),
+                  name);
+}
+
 qm_status qmatmul_gemm(const qm_qweight* w, const uint16_t* x, int64_t m, float* y, void* stream) {
   qm_status st = check_weight(w, "qmatmul_gemm(w)");
   if (st != QM_OK) return st;

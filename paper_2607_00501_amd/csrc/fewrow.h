@@ -71,15 +71,16 @@ __device__ __forceinline__ half8v weight_frag(const uint32_t* d, int j, half2v s
 // registers allow: U steps of 4 XR activation and NM RT (W + 1) weight
 // registers in flight, NM RT (16 fragment + 4 per row tile accumulator)
 // ones, XR offsets.
+constexpr bool two_matrices(QgMode mode) { return mode == QgMode::kMoeGateUp || mode == QgMode::kSwiglu; }
 constexpr int waves_per_simd(int fmt, int rt, int xr, int u, int nm) {
   return u * (4 * xr + nm * rt * (fmt_bits(fmt) + 1)) + nm * rt * (16 + (xr + 3) / 4 * 4) + xr + 16 + 24 <= 128 ? 4 : 2;
 }
 template <int FMT, int RT, int XR, int U, QgMode MODE>
-constexpr int kWavesPerSimd = waves_per_simd(FMT, RT, XR, U, MODE == QgMode::kMoeGateUp ? 2 : 1);
+constexpr int kWavesPerSimd = waves_per_simd(FMT, RT, XR, U, two_matrices(MODE) ? 2 : 1);
 
 template <int FMT, int RT, int XR, int U, QgMode MODE>
 __device__ __forceinline__ void body(const QgemmArgs& p) {
-  constexpr int NM = MODE == QgMode::kMoeGateUp ? 2 : 1;
+  constexpr int NM = two_matrices(MODE) ? 2 : 1;
   constexpr int W = fmt_bits(FMT), CB = chunk_block_bytes(FMT);
   constexpr bool kFloat = fmt_float(FMT);
   constexpr int SP = 4 / RT;                              // sub-panels per panel
@@ -119,6 +120,10 @@ __device__ __forceinline__ void body(const QgemmArgs& p) {
       first = in ? p.gpanel[j] : first;
     }
     panel = gp - first;
+  } else if constexpr (MODE == QgMode::kSwiglu) {
+    row0 = static_cast<int64_t>(blockIdx.y) * BR;
+    rows = static_cast<int>(min<int64_t>(BR, p.M - row0));
+    xcd_group_member(blockIdx.x, padded_rows(mN) / kPanel, SP, &panel, &sub);
   } else {
     const int64_t ny = padded_rows(p.N) / kPanel * SP;
     const int64_t u = xcd_chunked(blockIdx.x, SP);
@@ -256,7 +261,9 @@ __device__ __forceinline__ void body(const QgemmArgs& p) {
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) lds[(wave * NM * TILES + (m * RT + rt) * MT + mt) * 64 + lane] = acc[m][rt][mt];
   __syncthreads();
-  const bool vec = MODE != QgMode::kDense || (mN % 4 == 0 && (reinterpret_cast<uintptr_t>(my) & 15u) == 0);
+  const bool vec = MODE == QgMode::kDense    ? mN % 4 == 0 && (reinterpret_cast<uintptr_t>(my) & 15u) == 0
+                   : MODE == QgMode::kSwiglu ? mN % 4 == 0 && (reinterpret_cast<uintptr_t>(p.h) & 7u) == 0
+                                             : true;
   for (int e = tid; e < TILES * 64; e += kWaves * 64) {
     const int tile = e >> 6, l = e & 63;
     const int token = 16 * (tile % MT) + (l & 15);
@@ -280,11 +287,18 @@ __device__ __forceinline__ void body(const QgemmArgs& p) {
         for (int i = 0; i < 4; ++i)
           if (n + i < mN) dst[i] = v[0][i];
       }
-    } else if constexpr (MODE == QgMode::kMoeGateUp) {
+    } else if constexpr (two_matrices(MODE)) {
       uint16_t o[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) o[i] = h16(v[0][i] / (1.0f + expf(-v[0][i])) * v[NM - 1][i]);
-      *reinterpret_cast<uint2*>(p.h + r * mN + n) = make_uint2(o[0] | o[1] << 16, o[2] | o[3] << 16);
+      for (int i = 0; i < 4; ++i) o[i] = h16(qg::silu_mul(v[0][i], v[NM - 1][i]));
+      uint16_t* dst = p.h + r * mN + n;
+      if (vec) {
+        *reinterpret_cast<uint2*>(dst) = make_uint2(o[0] | o[1] << 16, o[2] | o[3] << 16);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (n + i < mN) dst[i] = o[i];
+      }
     } else {
       // An assignment whose bucket is not the expert topk_ids names gets a
       // NaN weight, so its token's output row is NaN.

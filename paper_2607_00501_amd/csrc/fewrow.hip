@@ -72,6 +72,54 @@ FewrowPlan fewrow_plan(int32_t fmt, int64_t m, int64_t n, int64_t k, int cu_coun
   return FewrowPlan{0, 0, 1};
 }
 
+// kSwiglu on the few-row kernel (a.q / a.q2: gate / up).
+#define QM_FEWROW_SWIGLU_TILES(X) X(1, 4) X(2, 4) X(2, 8)
+
+// Every workgroup covers its rows of both matrices.  As in fewrow_plan, the
+// first tile whose grid fits one workgroup per CU (Q4 2048 -> 2 x 8192: m = 16
+// 9.3 -> 6.9 us against the grouped call and the elementwise kernel, 32 11.3 ->
+// 8.5; the MFMA tiles take 14.2 and 15.6); 32-row blocks also with two per CU
+// (m = 64: 14.8 -> 13.6, tiles 14.9), but not for Q8 and the float formats (Q8:
+// 18.6, tiles 17.2).
+FewrowPlan fewrow_swiglu_plan(int32_t fmt, int64_t m, int64_t n, int cu_count) {
+  const int64_t panels = padded_rows(n) / kPanel;
+  auto groups = [&](int rt, int xr) { return panels * (4 / rt) * ((m + 4 * xr - 1) / (4 * xr)); };
+#define QM_FR(RT, XR) \
+  if (groups(RT, XR) <= cu_count) return FewrowPlan{RT, XR, 1};
+  QM_FEWROW_SWIGLU_TILES(QM_FR)
+#undef QM_FR
+  if (groups(2, 8) <= 2 * cu_count && fmt_bits(fmt) < 8) return FewrowPlan{2, 8, 1};
+  return FewrowPlan{0, 0, 1};
+}
+
+hipError_t launch_fewrow_swiglu(const QgemmArgs& a, int32_t fmt, const FewrowPlan& f, hipStream_t st) {
+  auto go = [&](auto ft) -> hipError_t {
+    constexpr int FMT = decltype(ft)::value;
+    const unsigned panels = static_cast<unsigned>(padded_rows(a.N) / kPanel);
+#define QM_FR(RT, XR)                                                                                             \
+  if (f.rt == RT && f.xr == XR) {                                                                                 \
+    hipLaunchKernelGGL((fewrow_kernel<FMT, RT, XR, 1, QgMode::kSwiglu>),                                          \
+                       dim3(panels * (4 / RT), static_cast<unsigned>((a.M + 4 * XR - 1) / (4 * XR))),             \
+                       dim3(fr::kWaves * 64), 0, st, a);                                                          \
+    return hipGetLastError();                                                                                     \
+  }
+    QM_FEWROW_SWIGLU_TILES(QM_FR)
+#undef QM_FR
+    return hipErrorInvalidConfiguration;
+  };
+  switch (fmt) {
+    case QM_Q4_G32: return go(std::integral_constant<int, QM_Q4_G32>{});
+    case QM_Q8_G32: return go(std::integral_constant<int, QM_Q8_G32>{});
+    case QM_Q2_G32: return go(std::integral_constant<int, QM_Q2_G32>{});
+    case QM_Q3_G32: return go(std::integral_constant<int, QM_Q3_G32>{});
+    case QM_Q5_G32: return go(std::integral_constant<int, QM_Q5_G32>{});
+    case QM_Q6_G32: return go(std::integral_constant<int, QM_Q6_G32>{});
+    case QM_F16: return go(std::integral_constant<int, QM_F16>{});
+    case QM_BF16: return go(std::integral_constant<int, QM_BF16>{});
+    default: return hipErrorInvalidValue;
+  }
+}
+
 hipError_t launch_fewrow(const QgemmArgs& a, int32_t fmt, const FewrowPlan& f, hipStream_t st) {
   switch (fmt) {
     case QM_Q4_G32: return launch_fmt<QM_Q4_G32>(a, f, st);

@@ -43,7 +43,10 @@
 //    same columns and the epilogue writes fp16 silu(gate) * up); kMoeDown
 //    (A = the fp16 h rows of the bucket, the epilogue scales by the
 //    assignment's gate weight and scatters the row, in fp16, to its
-//    assignment slot).
+//    assignment slot); kSwiglu (dense rows; half of a workgroup's wavefronts
+//    take gate panels, the other half the up panels of the same columns, each
+//    on the full row tile as in kDense, and the epilogue swaps halves of the
+//    two blocks through LDS and writes fp16 silu(gate) * up).
 //    MoE workgroups find their (expert, row tile) from the per-expert counts
 //    on the device, so no host synchronisation is needed.
 #pragma once
@@ -56,7 +59,7 @@
 
 namespace qm {
 
-enum class QgMode { kDense = 0, kMoeGateUp = 1, kMoeDown = 2 };
+enum class QgMode { kDense = 0, kMoeGateUp = 1, kMoeDown = 2, kSwiglu = 3 };
 
 struct QgemmArgs {
   const uint8_t* q;  const uint16_t* s;    // dense weights; MoE gate or down experts
@@ -81,11 +84,12 @@ struct QgemmArgs {
   const uint8_t* gq[kGemmGroupMax];
   const uint16_t* gs[kGemmGroupMax];
   float* gy[kGemmGroupMax];
-  int64_t gn[kGemmGroupMax];
+  int64_t gn[kGemmGroupMax];               // kSwiglu: matrix 0 gate, 1 up, output h
 };
 
 // Dense launch of the few-row kernel (fewrow.h).
 hipError_t launch_fewrow(const QgemmArgs& a, int32_t fmt, const FewrowPlan& f, hipStream_t st);
+hipError_t launch_fewrow_swiglu(const QgemmArgs& a, int32_t fmt, const FewrowPlan& f, hipStream_t st);
 
 namespace qg {
 
@@ -244,6 +248,26 @@ __device__ inline half8v dequant_crumb(uint32_t cw, uint32_t hb, int s, half2v s
   return half8v{q[0][0], q[0][1], q[1][0], q[1][1], q[2][0], q[2][1], q[3][0], q[3][1]};
 }
 
+// silu(g) * u by the hardware's base-2 exponential and reciprocal (about 1 ulp
+// each; the result is rounded to fp16).  The library expf and an IEEE division
+// cost about 35 VALU instructions per element, 4 us of the fused 2048 ->
+// 2 x 8192 product at 512 rows.
+__device__ __forceinline__ float silu_mul(float g, float u) {
+  return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(g * -1.4426950408889634f)) * u;
+}
+
+// fp16 stores of a 32x32 tile's register pair (r, r + 1) of rows row, row + 1
+// and the lane's column: neighbouring lanes swap one value, so that an even
+// lane holds row `row` of its column and the next, an odd lane row `row + 1` of
+// the previous and its own, and each stores one dword (64 2-byte stores per
+// lane and 128 x 64 block become 32 dwords).
+__device__ __forceinline__ uint32_t pair_halves(float a, float b, int lane) {
+  auto bits = [](float f) { return static_cast<uint32_t>(__builtin_bit_cast(uint16_t, static_cast<_Float16>(f))); };
+  const uint32_t own = bits(a) | bits(b) << 16;
+  const uint32_t nb = __builtin_amdgcn_mov_dpp(own, 0xB1, 0xF, 0xF, false);      // quad_perm [1,0,3,2]
+  return lane & 1 ? __builtin_amdgcn_perm(own, nb, 0x07060302u) : __builtin_amdgcn_perm(nb, own, 0x05040100u);
+}
+
 // Wavefront 0 maps the workgroup's linear tile index to (expert, row tile)
 // in expert order, with ceil(count / BM) tiles per expert.  Expert -1 when
 // the index lies beyond the last tile.
@@ -322,8 +346,11 @@ struct Cfg {
                                 : kFloat ? kNB * 2 * 2 * 2 : kNB * 2 * 2 * (kPlaneLoads + 1);
   // Split-K partial sums of slices 1..WK-1, in halves (fp32 = 2 halves).
   static constexpr int kRedHalves = (WK - 1) * WN * kTM * 2 * kNB * 16 * 64 * 2;
-  static constexpr int kLdsHalves =
-      kAStages * kStageBytes / 2 > kRedHalves ? kAStages * kStageBytes / 2 : kRedHalves;
+  // kSwiglu: half of every wavefront's block of slice 0.
+  static constexpr int kSwapHalves = MODE == QgMode::kSwiglu ? WN * kTM * 16 * 64 * 2 : 0;
+  static constexpr int kLdsMax = kRedHalves > kSwapHalves ? kRedHalves : kSwapHalves;
+  static constexpr int kLdsHalves = kAStages * kStageBytes / 2 > kLdsMax ? kAStages * kStageBytes / 2 : kLdsMax;
+  static_assert(MODE != QgMode::kSwiglu || (WN % 2 == 0 && kTM % 2 == 0), "kSwiglu pairs wavefronts and splits rows");
   static_assert(kAStages == kSlots || (kAStages == 2 && DEPTH == 2), "A stage schedule");
 };
 
@@ -350,7 +377,7 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
   int rows = 0;
   int expert = 0;
   int64_t col_block;
-  if constexpr (MODE == QgMode::kDense) {
+  if constexpr (MODE == QgMode::kDense || MODE == QgMode::kSwiglu) {
     row0 = static_cast<int64_t>(blockIdx.y) * BM;
     rows = static_cast<int>(min<int64_t>(BM, p.M - row0));
     col_block = blockIdx.x;
@@ -392,6 +419,13 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
     }
     n_wave = static_cast<int64_t>(gp - first) * kPanel;
     cols_ok = gp < p.gpanel[p.gcount];
+  }
+  if constexpr (MODE == QgMode::kSwiglu) {
+    const bool up = wn >= WN / 2;
+    mq = up ? p.gq[1] : p.gq[0];
+    ms = up ? p.gs[1] : p.gs[0];
+    n_wave = (col_block * (WN / 2) + wn % (WN / 2)) * kPanel;
+    cols_ok = n_wave < npad;
   }
   const int64_t mnpad = padded_rows(mN);
   // kMoeDown: assignment id and gate weight of each row of the tile, staged
@@ -801,9 +835,9 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
           for (int r = 0; r < 16; ++r) dst[((a * 2 * NB + b) * 16 + r) * 64 + lane] = acc[a][b][r];
     }
     __syncthreads();
-    if (wk > 0) return;
+    if (MODE != QgMode::kSwiglu && wk > 0) return;
 #pragma unroll 1
-    for (int j = 1; j < WK; ++j) {
+    for (int j = 1; j < (wk > 0 ? 0 : WK); ++j) {
       const float* src = red + ((j - 1) * WN + wn) * per_wave;
 #pragma unroll
       for (int a = 0; a < C::kTM; ++a)
@@ -816,25 +850,84 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
 
   // Epilogue: lane l, register r of a 32x32 tile holds
   // row 8*(r/4) + 4*(l/32) + r%4, column l%32.
+  if constexpr (MODE == QgMode::kSwiglu) {
+    // The gate wavefront of a column panel finishes the upper half of the row
+    // tiles, its up wavefront the lower half: each hands the other half of its
+    // block over in LDS (the A stages, or the split-K sums, are used up).
+    constexpr int TH = C::kTM / 2, HALF = WN / 2, block = TH * 2 * 16 * 64;
+    float* const ex = reinterpret_cast<float*>(lds);
+    const bool up = wn >= HALF;
+    const bool pairs = mN % 2 == 0 && (reinterpret_cast<uintptr_t>(p.h) & 3u) == 0;
+    __syncthreads();
+    if (wk == 0) {
+#pragma unroll
+      for (int a = 0; a < TH; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            ex[wn * block + ((a * 2 + b) * 16 + r) * 64 + lane] = up ? acc[a][b][r] : acc[TH + a][b][r];
+    }
+    __syncthreads();
+    if (wk > 0) return;
+    const float* other = ex + (up ? wn - HALF : wn + HALF) * block + lane;
+#pragma unroll
+    for (int a = 0; a < TH; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const int64_t col = n_wave + 32 * b + (lane & 31);
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+          float hv[2];
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const float mine = up ? acc[TH + a][b][r + i] : acc[a][b][r + i];
+            const float theirs = other[((a * 2 + b) * 16 + r + i) * 64];
+            hv[i] = silu_mul(up ? theirs : mine, up ? mine : theirs);
+          }
+          const int lr = (up ? TH + a : a) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+          if (pairs) {                                     // (columns come in pairs: n is even)
+            const uint32_t v = pair_halves(hv[0], hv[1], lane);
+            if (lr + (lane & 1) < rows && col < mN)
+              *reinterpret_cast<uint32_t*>(p.h + (row0 + lr + (lane & 1)) * mN + (col & ~int64_t(1))) = v;
+          } else {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+              if (lr + i < rows && col < mN)
+                p.h[(row0 + lr + i) * mN + col] = __builtin_bit_cast(uint16_t, static_cast<_Float16>(hv[i]));
+          }
+        }
+      }
+    return;
+  }
 #pragma unroll
   for (int a = 0; a < C::kTM; ++a)
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       const int64_t col = n_wave + 32 * b + (lane & 31);
+      if constexpr (MODE == QgMode::kDense) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int lr = a * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (lr >= rows || col >= mN) continue;
-        if constexpr (MODE == QgMode::kDense) {
+        for (int r = 0; r < 16; ++r) {
+          const int lr = a * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
           // Y is not read again by this kernel: stream it past the caches.
-          __builtin_nontemporal_store(acc[a][b][r], my + (row0 + lr) * mN + col);
-        } else if constexpr (MODE == QgMode::kMoeGateUp) {
-          const float g = acc[a][b][r];
-          const float u = acc[a][2 + b][r];
-          const float hv = g / (1.0f + expf(-g)) * u;
-          p.h[(row0 + lr) * N + col] = __builtin_bit_cast(uint16_t, static_cast<_Float16>(hv));
-        } else {
-          p.yp[row_asg[lr] * N + col] = __builtin_bit_cast(uint16_t, static_cast<_Float16>(row_w[lr] * acc[a][b][r]));
+          if (lr < rows && col < mN) __builtin_nontemporal_store(acc[a][b][r], my + (row0 + lr) * mN + col);
+        }
+      } else {
+        // fp16 rows; N is a multiple of 32 (it is the K of the other product).
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+          const int lr0 = a * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+          float v[2];
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            if constexpr (MODE == QgMode::kMoeGateUp) v[i] = silu_mul(acc[a][b][r + i], acc[a][2 + b][r + i]);
+            else v[i] = row_w[lr0 + i] * acc[a][b][r + i];
+          }
+          const uint32_t hv = pair_halves(v[0], v[1], lane);
+          const int lr = lr0 + (lane & 1);
+          if (lr >= rows || col >= mN) continue;
+          const int64_t row = MODE == QgMode::kMoeGateUp ? row0 + lr : row_asg[MODE == QgMode::kMoeDown ? lr : 0];
+          *reinterpret_cast<uint32_t*>((MODE == QgMode::kMoeGateUp ? p.h : p.yp) + row * mN + (col & ~int64_t(1))) = hv;
         }
       }
     }

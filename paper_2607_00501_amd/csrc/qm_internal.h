@@ -145,6 +145,9 @@ hipError_t launch_gemm(int32_t fmt, const uint8_t* q, const uint16_t* s, const u
 hipError_t launch_gemm_group(int32_t fmt, int count, const uint8_t* const* q, const uint16_t* const* s,
                              float* const* y, const int64_t* n, const uint16_t* x, int64_t m, int64_t k,
                              int cu_count, hipStream_t st);
+hipError_t launch_gemm_swiglu(int32_t fmt, const uint8_t* qg, const uint16_t* sg, const uint8_t* qu,
+                              const uint16_t* su, const uint16_t* x, uint16_t* h, int64_t m, int64_t n, int64_t k,
+                              int cu_count, hipStream_t st);
 
 // Decode attention: KV rows per workgroup slice and number of slices.
 constexpr int kAttnMaxSplits = 256;
@@ -254,6 +257,7 @@ bool gemm_plan_instantiated(const GemmPlan& p);   // a prefill GEMM tile exists 
 // workgroup, u steps in flight (rt = 0: take the tiles of gemm_plan).
 struct FewrowPlan { int rt; int xr; int u; };
 FewrowPlan fewrow_plan(int32_t fmt, int64_t m, int64_t n, int64_t k, int cu_count);
+FewrowPlan fewrow_swiglu_plan(int32_t fmt, int64_t m, int64_t n, int cu_count);
 const char* gemm_tile_name(int64_t m, int64_t n);
 const char* moe_tile_name(int64_t rows_per_expert);
 

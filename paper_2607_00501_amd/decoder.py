@@ -164,8 +164,8 @@ class DenseDecoder:
         shapes = dict(x=((c.hidden,), torch.float32), h=((c.hidden,), torch.float16),
                       q=((qd,), torch.float32), k=((kvd,), torch.float32), v=((kvd,), torch.float32),
                       qh=((qd,), torch.float16), o16=((qd,), torch.float16),
-                      ya=((c.hidden,), torch.float32), g=((c.inter,), torch.float32),
-                      u=((c.inter,), torch.float32), sw=((c.inter,), torch.float16), y=((c.hidden,), torch.float32))
+                      ya=((c.hidden,), torch.float32), sw=((c.inter,), torch.float16),
+                      y=((c.hidden,), torch.float32))
         if self._chunk is None:
             dev = self.emb.device
             self._chunk = {n: torch.empty(self.max_chunk * sh[0], dtype=dt, device=dev)
@@ -205,8 +205,8 @@ class DenseDecoder:
                                            workspace=b["attn_ws"], stream=s)
             ya = B.qmatmul_gemm(ly.wo, o16, out=b["ya"], stream=s)
             h = B.qdec_rmsnorm(x, ly.ffn_norm, c.eps, residual=ya, out=b["h"], stream=s)
-            g, u = B.qmatmul_gemm_grouped([ly.wg, ly.wu], h, outs=[b["g"], b["u"]], stream=s)
-            y = B.qmatmul_gemm(ly.wd, B.qdec_swiglu_f16(g, u, out=b["sw"], stream=s), out=b["y"], stream=s)
+            sw = B.qmatmul_gemm_swiglu_f16(ly.wg, ly.wu, h, out=b["sw"], stream=s)
+            y = B.qmatmul_gemm(ly.wd, sw, out=b["y"], stream=s)
         B.qdec_rmsnorm(x[m - 1], self.norm, c.eps, residual=y[m - 1], out=self.h, stream=s)
         B.qmatmul_gemv(self.lm_head, self.h, out=self.logits, stream=s)
         B.qdec_argmax(self.logits, out=self.token, workspace=self.argmax_ws, stream=s)

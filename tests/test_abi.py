@@ -415,3 +415,21 @@ def test_prefill_glue_validation():
     assert L.qdec_swiglu_f16(p, p, -1, p, None) == 2 and L.qdec_swiglu_f16(None, p, 4, p, None) == 1
     assert L.qdec_swiglu_f16(p, p, 4, ctypes.c_void_p(0x50001), None) == 3
     assert B.qm_last_error()
+
+
+def test_gemm_swiglu_validation():
+    L = B.lib()
+    p = ctypes.c_void_p(0x50000)
+
+    def call(g, u, x=p, m=4, h=p):
+        return L.qmatmul_gemm_swiglu_f16(ctypes.byref(g.c() if hasattr(g, "c") else g),
+                                         ctypes.byref(u.c() if hasattr(u, "c") else u), x, m, h, None)
+
+    w = _fake_weight()
+    assert call(w, w, m=0) == 2 and call(w, w, m=65537) == 2           # m out of range
+    assert call(w, _fake_weight(fmt=2)) == 4                           # formats differ
+    assert call(w, _fake_weight(k=96)) == 2                            # shapes differ
+    assert call(w, _fake_weight(layout=0)) == 5                        # not DEVICE layout
+    assert call(w, w, x=None) == 1 and call(w, w, h=None) == 1         # null
+    assert call(w, w, x=ctypes.c_void_p(0x50008)) == 3                 # x misaligned
+    assert call(w, w, h=ctypes.c_void_p(0x50001)) == 3                 # h misaligned

@@ -1,0 +1,70 @@
+"""GPU parity of the gate/up product with the SwiGLU epilogue: every tile of
+its plan at ragged rows and columns, each format, unaligned and odd-width
+outputs."""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import qmatmul_oracle as O
+from paper_2607_00501_amd import binding as B
+from paper_2607_00501_amd import inputs
+from tests.helpers import MFMA_TOL, rel_err
+
+pytestmark = pytest.mark.gpu
+
+FORMATS = [(O.Q4, B.Q4_G32), (O.Q8, B.Q8_G32), (O.Q2, B.Q2_G32), (O.Q3, B.Q3_G32), (O.Q5, B.Q5_G32),
+           (O.Q6, B.Q6_G32), (O.F16, B.F16), (O.BF16, B.BF16)]
+
+
+def _weights(seed, n, k, fmt):
+    out = []
+    for i in (0, 1):
+        w = inputs.weights_np(seed + i, (n, k), sigma=0.05)
+        q, s = O.quantise(w, fmt[0])
+        dev = B.qm_repack(B.qm_quantise(torch.from_numpy(w).cuda(), fmt[1]), B.LAYOUT_DEVICE)
+        out.append(((O.pack(q, fmt[0]), s), dev))
+    return out
+
+
+def _check(m, n, k, fmt, offset=0):
+    (g, wg), (u, wu) = _weights(17 * m + n, n, k, fmt)
+    x = inputs.activations_np(5 * m + k, (m, k))
+    buf = torch.full((m * n + 8,), 9.0, dtype=torch.float16, device="cuda")
+    out = buf[offset:offset + m * n].view(m, n)
+    B.qmatmul_gemm_swiglu_f16(wg, wu, torch.from_numpy(x).cuda(), out=out)
+    G, U = O.gemm(*g, fmt[0], x), O.gemm(*u, fmt[0], x)
+    assert rel_err(out.cpu().numpy(), O.silu(G) * U) <= MFMA_TOL
+    rest = torch.cat([buf[:offset], buf[offset + m * n:]])
+    assert (rest == 9.0).all()
+
+
+@pytest.mark.parametrize("fmt", FORMATS, ids=lambda f: str(f[1]))
+@pytest.mark.parametrize("m,n,k", [
+    (1, 130, 96),           # the GEMV
+    (13, 1000, 160),        # few-row kernel, 16-row sub-panels, partial last step
+    (30, 3072, 96),         # 32-row sub-panels
+    (61, 3072, 128),        # 32-row blocks
+    (100, 5000, 96),        # 64 x 128, 2-way split-K (an odd number of panels)
+    (300, 5000, 96),        # 64 x 256, ragged rows
+    (590, 5000, 64),        # 128 x 256, ragged rows, an odd number of panels
+])
+def test_swiglu_gemm_parity(fmt, m, n, k):
+    _check(m, n, k, fmt)
+
+
+@pytest.mark.parametrize("m,n,offset", [(9, 65, 1), (16, 66, 2), (70, 6499, 1), (100, 5001, 0),
+                                         (300, 5002, 1), (590, 4999, 0)])
+def test_swiglu_gemm_odd_width_and_alignment(m, n, offset):
+    _check(m, n, 64, (O.Q4, B.Q4_G32), offset)
+
+
+def test_swiglu_gemm_extreme_gates():
+    """Gates far outside the exponential's range: silu goes to 0 or g."""
+    m, n, k = 20, 64, 64
+    (g, wg), (u, wu) = _weights(3, n, k, (O.F16, B.F16))
+    x = inputs.activations_np(4, (m, k)) * np.float16(300)
+    y = B.qmatmul_gemm_swiglu_f16(wg, wu, torch.from_numpy(x).cuda()).cpu().numpy().astype(np.float64)
+    ref = (O.silu(O.gemm(*g, O.F16, x)) * O.gemm(*u, O.F16, x))
+    ok = np.abs(ref) < 60000
+    assert ok.mean() > 0.5 and np.abs(y - ref)[ok].max() <= MFMA_TOL * np.abs(ref[ok]).max()
