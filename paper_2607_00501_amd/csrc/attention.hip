@@ -12,16 +12,20 @@
 //    16-byte load each (fully coalesced, 4 or 8 rows per wavefront load);
 //  * workgroup (split, g) takes a slice of rows of KV head g for all G query
 //    heads of the group, so each K and V byte is read once per step;
-//  * scores: per lane a partial dot product of its 8 dimensions
-//    (v_dot2_f32_f16 against the query slice held in registers), summed over
-//    the row's lanes with cross-lane adds, scaled into the base-2 domain and
-//    kept in LDS; then per head the slice maximum, p = 2^(s - m) and their
-//    sum; then acc = sum_t p_t v_t in fp32 registers, summed over lanes and
-//    wavefronts;
+//  * what bounds it is latency until the cache is tens of MB: the loads of the
+//    next rows are in flight while a wavefront works on the present ones, each
+//    group of D/8 lanes runs online softmax over its own rows (base-2 domain,
+//    fp32), and nothing but the row sums crosses lanes in the loop (per lane a
+//    partial dot product of its 8 dimensions by v_dot2_f32_f16, summed by DPP);
 //  * each workgroup writes (acc, m, l) of its slice to the caller's
 //    workspace, and a second kernel merges the slices exactly as online
 //    softmax does: M = max m_i, L = sum l_i 2^(m_i - M), o = sum acc_i
 //    2^(m_i - M) / L.
+// Measured against scores, softmax and P V as three phases with the scores in
+// LDS and a merge of one thread per dimension (us per call, K and V from HBM):
+// 16 / 8 heads of 128: 9.3 -> 7.1 at 700 rows, 15.8 -> 11.6 at 6,007, 20.1 ->
+// 18.0 at 16,384, 58.7 -> 56 at 65,536; 32 / 8 heads of 64: 10.8 -> 7.7 at 700,
+// 16.9 -> 15.1 at 16,384; 64 / 8 heads of 128: 14.0 -> 11.2 at 700.
 #include "qm_internal.h"
 
 #include <hip/hip_fp16.h>
@@ -29,12 +33,15 @@
 #include <algorithm>
 #include <cfloat>
 #include <cmath>
+#include <type_traits>
 
 namespace qm {
 namespace {
 
 constexpr int kAttnWaves = 4;
-constexpr int kAttnUnroll = 4;    // row loads in flight per lane
+template <int G> constexpr int kAttnDirectWaves = G <= 4 ? 8 : 4;   // a whole cache in one slice
+// Row loads of K and of V in flight per lane and step.
+template <int G> constexpr int kAttnUnroll = G <= 4 ? 4 : 2;
 
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
@@ -58,24 +65,75 @@ __device__ __forceinline__ void store_out(float* o, uint16_t* o16, int64_t i, fl
   }
 }
 
-template <int D, int G>
-__global__ __launch_bounds__(kAttnWaves * 64) void attn_decode_split_kernel(
+// Sum over the LPR lanes (8 or 16, aligned) that share a cache row, by lane
+// permutes inside the VALU; every lane gets the same bits.
+template <int LPR>
+__device__ __forceinline__ float row_sum(float v) {
+  auto add = [](float x, auto ctrl) __attribute__((always_inline)) {
+    return x + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), decltype(ctrl)::value,
+                                                                  0xF, 0xF, false));
+  };
+  v = add(v, std::integral_constant<int, 0xB1>{});        // quad_perm [1,0,3,2]
+  v = add(v, std::integral_constant<int, 0x4E>{});        // quad_perm [2,3,0,1]
+  v = add(v, std::integral_constant<int, 0x141>{});       // row_half_mirror
+  if constexpr (LPR == 16) v = add(v, std::integral_constant<int, 0x140>{});   // row_mirror
+  return v;
+}
+
+// op over the lanes l, l ^ LPR, ... of a wavefront (the row groups), on every lane.
+template <int LPR, class Op>
+__device__ __forceinline__ float across_groups(float v, Op op) {
+  if constexpr (LPR == 8)
+    v = op(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x128, 0xF, 0xF, false)));
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+// Cache rows a wavefront takes per step: kAttnUnroll row loads per lane.
+template <int D, int G> constexpr int kAttnStepRows = 64 / (D / 8) * kAttnUnroll<G>;
+
+// WAVES wavefronts stream a slice of tc rows of one KV head for its G query
+// heads.  A wavefront takes every WAVES-th step of kAttnStepRows rows, its K
+// and V rows of the next step loading while it works on this one; each group
+// of D / 8 lanes keeps a running maximum, sum and accumulator of its own rows
+// (online softmax), so nothing crosses lanes in the loop but the row sums and
+// no barrier stands in it.  The groups and wavefronts meet once at the end.
+template <int D, int G, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void attn_decode_split_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     int64_t len, int64_t max_len, int tc, int nsplit, float scale_log2, float* __restrict__ ws,
     float* __restrict__ o, uint16_t* __restrict__ o16) {
   constexpr int LPR = D / 8;                 // lanes per cache row
   constexpr int RPW = 64 / LPR;              // rows per wavefront load
-  constexpr int RPI = kAttnWaves * RPW;      // rows per workgroup load
-  extern __shared__ float sc[];              // [G][tc] scores, then p
-  __shared__ float stat[G][2];               // per head: slice maximum (base 2) and sum of p
-  __shared__ float part[kAttnWaves][G][D];
+  constexpr int UN = kAttnUnroll<G>, RS = kAttnStepRows<D, G>;
+  __shared__ float part[WAVES][G][D];
+  __shared__ float stat[WAVES][G][2];        // maximum (base 2) and sum
 
   const int split = blockIdx.x, g = blockIdx.y;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int sub = lane % LPR, rw = lane / LPR;
   const int64_t t0 = static_cast<int64_t>(split) * tc;
   const int nrows = static_cast<int>(min<int64_t>(tc, len - t0));
 
+  const int64_t head_row0 = static_cast<int64_t>(g) * max_len + t0;
+  const uint16_t* kb = k + head_row0 * D + sub * 8;
+  const uint16_t* vb = v + head_row0 * D + sub * 8;
+  struct Rows { uint4 k[UN], v[UN]; };
+  // Rows past the slice re-read its last row and count nothing.
+  auto load = [&](int r0) __attribute__((always_inline)) {
+    Rows x;
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int64_t r = static_cast<int64_t>(min(r0 + u * RPW + rw, nrows - 1)) * D;
+      x.k[u] = *reinterpret_cast<const uint4*>(kb + r);
+      x.v[u] = *reinterpret_cast<const uint4*>(vb + r);
+    }
+    return x;
+  };
+  Rows cur = load(wave * RS);
   // Query slices of the G heads: dimensions 8 sub .. 8 sub + 7.
   half2v qf[G][4];
 #pragma unroll
@@ -84,202 +142,178 @@ __global__ __launch_bounds__(kAttnWaves * 64) void attn_decode_split_kernel(
     qf[j][0] = __builtin_bit_cast(half2v, t.x); qf[j][1] = __builtin_bit_cast(half2v, t.y);
     qf[j][2] = __builtin_bit_cast(half2v, t.z); qf[j][3] = __builtin_bit_cast(half2v, t.w);
   }
-  const int64_t head_row0 = static_cast<int64_t>(g) * max_len + t0;
-  const uint16_t* kb = k + head_row0 * D + sub * 8;
-  const uint16_t* vb = v + head_row0 * D + sub * 8;
 
-  // Scores, kAttnUnroll row loads in flight per lane (rows past the slice
-  // re-read its last row and are not stored).  The V rows of the first block
-  // are loaded together with its K rows, so that a slice of one block costs
-  // one memory round trip.
-  uint4 vpre[kAttnUnroll];
-  for (int r0 = 0; r0 < nrows; r0 += RPI * kAttnUnroll) {
-    uint4 kv[kAttnUnroll];
+  float m[G], l[G], acc[G][8];
 #pragma unroll
-    for (int u = 0; u < kAttnUnroll; ++u) {
-      const int r = min(r0 + u * RPI + wave * RPW + rw, nrows - 1);
-      kv[u] = *reinterpret_cast<const uint4*>(kb + static_cast<int64_t>(r) * D);
-    }
-    if (r0 == 0) {
-#pragma unroll
-      for (int u = 0; u < kAttnUnroll; ++u) {
-        const int r = min(u * RPI + wave * RPW + rw, nrows - 1);
-        vpre[u] = *reinterpret_cast<const uint4*>(vb + static_cast<int64_t>(r) * D);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kAttnUnroll; ++u) {
-      const int r = r0 + u * RPI + wave * RPW + rw;
-      float s[G];
-#pragma unroll
-      for (int j = 0; j < G; ++j) {
-        float a = __builtin_amdgcn_fdot2(qf[j][0], __builtin_bit_cast(half2v, kv[u].x), 0.0f, false);
-        a = __builtin_amdgcn_fdot2(qf[j][1], __builtin_bit_cast(half2v, kv[u].y), a, false);
-        a = __builtin_amdgcn_fdot2(qf[j][2], __builtin_bit_cast(half2v, kv[u].z), a, false);
-        a = __builtin_amdgcn_fdot2(qf[j][3], __builtin_bit_cast(half2v, kv[u].w), a, false);
-#pragma unroll
-        for (int off = 1; off < LPR; off <<= 1) a += __shfl_xor(a, off);
-        s[j] = a;
-      }
-      if (sub == 0 && r < nrows) {
-#pragma unroll
-        for (int j = 0; j < G; ++j) sc[j * tc + r] = s[j] * scale_log2;
-      }
-    }
-  }
-  __syncthreads();
-
-  // Per head: slice maximum, p = 2^(s - m), sum of p.
-  for (int j = wave; j < G; j += kAttnWaves) {
-    float m = -INFINITY;
-    for (int t = lane; t < nrows; t += 64) m = fmaxf(m, sc[j * tc + t]);
-    m = wave_max(m);
-    float l = 0.0f;
-    for (int t = lane; t < nrows; t += 64) {
-      const float p = exp2f(sc[j * tc + t] - m);
-      sc[j * tc + t] = p;
-      l += p;
-    }
-    l = wave_sum(l);
-    if (lane == 0) { stat[j][0] = m; stat[j][1] = l; }
-  }
-  __syncthreads();
-
-  // acc = sum_t p_t v_t over the slice.
-  float acc[G][8];
-#pragma unroll
-  for (int j = 0; j < G; ++j)
+  for (int j = 0; j < G; ++j) {
+    m[j] = -FLT_MAX;                         // finite: a group without rows adds 0, not NaN
+    l[j] = 0.0f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[j][i] = 0.0f;
-  for (int r0 = 0; r0 < nrows; r0 += RPI * kAttnUnroll) {
-    uint4 vv[kAttnUnroll];
+  }
+  for (int r0 = wave * RS; r0 < nrows; r0 += WAVES * RS) {
+    const Rows x = cur;
+    if (r0 + WAVES * RS < nrows) cur = load(r0 + WAVES * RS);
+    float s[G][UN];
 #pragma unroll
-    for (int u = 0; u < kAttnUnroll; ++u) {
-      const int r = min(r0 + u * RPI + wave * RPW + rw, nrows - 1);
-      vv[u] = r0 == 0 ? vpre[u] : *reinterpret_cast<const uint4*>(vb + static_cast<int64_t>(r) * D);
+    for (int u = 0; u < UN; ++u) {
+      const bool ok = r0 + u * RPW + rw < nrows;
+#pragma unroll
+      for (int j = 0; j < G; ++j) {
+        float a = __builtin_amdgcn_fdot2(qf[j][0], __builtin_bit_cast(half2v, x.k[u].x), 0.0f, false);
+        a = __builtin_amdgcn_fdot2(qf[j][1], __builtin_bit_cast(half2v, x.k[u].y), a, false);
+        a = __builtin_amdgcn_fdot2(qf[j][2], __builtin_bit_cast(half2v, x.k[u].z), a, false);
+        a = __builtin_amdgcn_fdot2(qf[j][3], __builtin_bit_cast(half2v, x.k[u].w), a, false);
+        s[j][u] = ok ? row_sum<LPR>(a) * scale_log2 : -INFINITY;
+      }
     }
 #pragma unroll
-    for (int u = 0; u < kAttnUnroll; ++u) {
-      const int r = r0 + u * RPI + wave * RPW + rw;
-      const bool ok = r < nrows;
-      const int rc = ok ? r : nrows - 1;
-      const uint32_t w[4] = {vv[u].x, vv[u].y, vv[u].z, vv[u].w};
-      float vf[8];
+    for (int j = 0; j < G; ++j) {
+      float mn = m[j];
+#pragma unroll
+      for (int u = 0; u < UN; ++u) mn = fmaxf(mn, s[j][u]);
+      const float alpha = __builtin_amdgcn_exp2f(m[j] - mn);
+      m[j] = mn;
+      l[j] *= alpha;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[j][i] *= alpha;
+#pragma unroll
+      for (int u = 0; u < UN; ++u) {
+        s[j][u] = __builtin_amdgcn_exp2f(s[j][u] - mn);
+        l[j] += s[j][u];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const uint32_t w[4] = {x.v[u].x, x.v[u].y, x.v[u].z, x.v[u].w};
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const half2v h = __builtin_bit_cast(half2v, w[i]);
-        vf[2 * i] = static_cast<float>(h[0]);
-        vf[2 * i + 1] = static_cast<float>(h[1]);
-      }
 #pragma unroll
-      for (int j = 0; j < G; ++j) {
-        const float p = ok ? sc[j * tc + rc] : 0.0f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[j][i] = fmaf(p, vf[i], acc[j][i]);
+        for (int j = 0; j < G; ++j) {
+          acc[j][2 * i] = fmaf(s[j][u], static_cast<float>(h[0]), acc[j][2 * i]);
+          acc[j][2 * i + 1] = fmaf(s[j][u], static_cast<float>(h[1]), acc[j][2 * i + 1]);
+        }
       }
     }
   }
-  // Lanes with the same dimension slice (equal sub) hold different rows.
+  // The row groups of the wavefront, then the wavefronts.  V rows that were
+  // read clamped carry weight 0 (an infinite V there gives NaN, as the last
+  // row itself does).
 #pragma unroll
-  for (int j = 0; j < G; ++j)
+  for (int j = 0; j < G; ++j) {
+    const float mw = across_groups<LPR>(m[j], [](float a, float b) { return fmaxf(a, b); });
+    const float f = __builtin_amdgcn_exp2f(m[j] - mw);
+    auto plus = [](float a, float b) { return a + b; };
+    const float lw = across_groups<LPR>(l[j] * f, plus);
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-      for (int off = LPR; off < 64; off <<= 1) acc[j][i] += __shfl_xor(acc[j][i], off);
-  if (rw == 0) {
-#pragma unroll
-    for (int j = 0; j < G; ++j)
+    for (int i = 0; i < 8; ++i) acc[j][i] = across_groups<LPR>(acc[j][i] * f, plus);
+    if (rw == 0) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) part[wave][j][sub * 8 + i] = acc[j][i];
+      if (sub == 0) {
+        stat[wave][j][0] = mw;
+        stat[wave][j][1] = lw;
+      }
+    }
   }
   __syncthreads();
-  if (o || o16) {   // a single slice covers the whole cache: normalise and write the output
-    for (int e = threadIdx.x; e < G * D; e += kAttnWaves * 64) {
-      const int j = e / D, d = e % D;
-      float a = part[0][j][d];
-#pragma unroll
-      for (int w2 = 1; w2 < kAttnWaves; ++w2) a += part[w2][j][d];
-      store_out(o, o16, (static_cast<int64_t>(g) * G + j) * D + d, a / stat[j][1]);
-    }
-    return;
-  }
-  for (int e = threadIdx.x; e < G * D; e += kAttnWaves * 64) {
+  for (int e = threadIdx.x; e < G * D; e += WAVES * 64) {
     const int j = e / D, d = e % D;
-    float a = part[0][j][d];
+    float mx = stat[0][j][0];
 #pragma unroll
-    for (int w2 = 1; w2 < kAttnWaves; ++w2) a += part[w2][j][d];
-    ws[((static_cast<int64_t>(g) * G + j) * nsplit + split) * (D + 2) + d] = a;
-  }
-  if (threadIdx.x < G) {
-    float* st = ws + ((static_cast<int64_t>(g) * G + threadIdx.x) * nsplit + split) * (D + 2) + D;
-    st[0] = stat[threadIdx.x][0];
-    st[1] = stat[threadIdx.x][1];
+    for (int w = 1; w < WAVES; ++w) mx = fmaxf(mx, stat[w][j][0]);
+    float a = 0.0f, ls = 0.0f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+      const float f = __builtin_amdgcn_exp2f(stat[w][j][0] - mx);
+      a = fmaf(part[w][j][d], f, a);
+      ls = fmaf(stat[w][j][1], f, ls);
+    }
+    const int64_t h = static_cast<int64_t>(g) * G + j;
+    if (o || o16) {   // a single slice covers the whole cache: normalise and write the output
+      store_out(o, o16, h * D + d, a / ls);
+    } else {
+      ws[(h * nsplit + split) * D + d] = a;
+      if (d < 2) ws[static_cast<int64_t>(gridDim.y) * G * nsplit * D + (h * nsplit + split) * 2 + d] = d ? ls : mx;
+    }
   }
 }
 
-// Merge of the slices of one query head (thread d: output dimension d).
-// The slice statistics go to LDS in one round of loads; the partial sums of
-// all slices are then loaded independently of each other (eight in flight
-// per thread), so the merge costs a few memory round trips, not one per
-// slice.
+// Merge of the slices of one query head.  Workgroup = head: groups of D / 4
+// threads (4 dimensions each) take every kMergeGroups-th slice; every
+// wavefront finds the largest maximum by itself, so the loads of the partial
+// sums are in flight meanwhile and one barrier is left, before the groups are
+// added in order.
+constexpr int kMergeThreads = 512;
+
 template <int D>
-__global__ __launch_bounds__(D) void attn_decode_combine_kernel(const float* __restrict__ ws, int nsplit,
-                                                                 float* __restrict__ o, uint16_t* __restrict__ o16) {
-  __shared__ float wt[kAttnMaxSplits];
-  __shared__ float red[2][D / 64];
-  const int h = blockIdx.x, d = threadIdx.x, lane = d & 63, wv = d >> 6;
-  const float* base = ws + static_cast<int64_t>(h) * nsplit * (D + 2);
-  float mloc = -INFINITY;
-  float lv[kAttnMaxSplits / D];
+__global__ __launch_bounds__(kMergeThreads) void attn_decode_combine_kernel(const float* __restrict__ ws, int nsplit,
+                                                                            float* __restrict__ o,
+                                                                            uint16_t* __restrict__ o16) {
+  constexpr int GROUPS = kMergeThreads / (D / 4), PER = 8;
+  __shared__ float4 part[GROUPS][D / 4];
+  __shared__ float lsum[GROUPS];
+  const int64_t h = blockIdx.x;
+  const int lane = threadIdx.x & 63, c = threadIdx.x % (D / 4), grp = threadIdx.x / (D / 4);
+  const float4* acc = reinterpret_cast<const float4*>(ws + h * nsplit * D);
+  const float2* st = reinterpret_cast<const float2*>(ws + static_cast<int64_t>(gridDim.x) * nsplit * D) + h * nsplit;
+  float mx = -FLT_MAX;
 #pragma unroll
-  for (int u = 0; u < kAttnMaxSplits / D; ++u) {
-    const int i = d + u * D;
-    const float m = i < nsplit ? base[i * (D + 2) + D] : -INFINITY;
-    lv[u] = i < nsplit ? base[i * (D + 2) + D + 1] : 0.0f;
-    if (i < nsplit) wt[i] = m;
-    mloc = fmaxf(mloc, m);
-  }
-  mloc = wave_max(mloc);
-  if (lane == 0) red[0][wv] = mloc;
-  __syncthreads();
-  float M = red[0][0];
+  for (int u = 0; u < kAttnMaxSplits / 64; ++u) mx = fmaxf(mx, st[min(u * 64 + lane, nsplit - 1)].x);
+  float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  float l = 0.0f;
+  mx = wave_max(mx);
+  for (int s0 = grp; s0 < nsplit; s0 += GROUPS * PER) {
+    float4 v[PER];
+    float2 t[PER];
 #pragma unroll
-  for (int w2 = 1; w2 < D / 64; ++w2) M = fmaxf(M, red[0][w2]);
-  float lpart = 0.0f;
+    for (int u = 0; u < PER; ++u) {
+      const int s = min(s0 + u * GROUPS, nsplit - 1);
+      v[u] = acc[s * (D / 4) + c];
+      t[u] = st[s];
+    }
 #pragma unroll
-  for (int u = 0; u < kAttnMaxSplits / D; ++u) {
-    const int i = d + u * D;
-    if (i < nsplit) {
-      const float e = exp2f(wt[i] - M);
-      wt[i] = e;
-      lpart = fmaf(e, lv[u], lpart);
+    for (int u = 0; u < PER; ++u) {
+      const float f = s0 + u * GROUPS < nsplit ? __builtin_amdgcn_exp2f(t[u].x - mx) : 0.0f;
+      l = fmaf(t[u].y, f, l);
+      a.x = fmaf(v[u].x, f, a.x);
+      a.y = fmaf(v[u].y, f, a.y);
+      a.z = fmaf(v[u].z, f, a.z);
+      a.w = fmaf(v[u].w, f, a.w);
     }
   }
-  lpart = wave_sum(lpart);
-  if (lane == 0) red[1][wv] = lpart;
+  part[grp][c] = a;
+  if (c == 0) lsum[grp] = l;
   __syncthreads();
-  float L = red[1][0];
+  if (threadIdx.x < D) {
+    const float* p = reinterpret_cast<const float*>(part);
+    float s = 0.0f, ls = 0.0f;
 #pragma unroll
-  for (int w2 = 1; w2 < D / 64; ++w2) L += red[1][w2];
-  float a = 0.0f;
-#pragma unroll 8
-  for (int i = 0; i < nsplit; ++i) a = fmaf(wt[i], base[i * (D + 2) + d], a);
-  store_out(o, o16, static_cast<int64_t>(h) * D + d, a / L);
+    for (int i = 0; i < GROUPS; ++i) {
+      s += p[i * D + threadIdx.x];
+      ls += lsum[i];
+    }
+    store_out(o, o16, h * D + threadIdx.x, s / ls);
+  }
 }
 
 template <int D, int G>
 hipError_t launch_decode_dg(const uint16_t* q, const uint16_t* k, const uint16_t* v, int hkv, int64_t len,
                             int64_t max_len, float scale, float* o, uint16_t* o16, float* ws, const AttnPlan& p,
                             hipStream_t st) {
-  const size_t lds = static_cast<size_t>(G) * p.tc * sizeof(float);
   const float sl2 = scale * 1.4426950408889634f;
-  float* od = p.nsplit == 1 ? o : nullptr;
-  uint16_t* od16 = p.nsplit == 1 ? o16 : nullptr;
-  hipLaunchKernelGGL((attn_decode_split_kernel<D, G>), dim3(p.nsplit, hkv), dim3(kAttnWaves * 64), lds, st,
-                     q, k, v, len, max_len, p.tc, p.nsplit, sl2, ws, od, od16);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || p.nsplit == 1) return e;
-  hipLaunchKernelGGL((attn_decode_combine_kernel<D>), dim3(hkv * G), dim3(D), 0, st, ws, p.nsplit, o, o16);
+  if (p.nsplit == 1) {
+    hipLaunchKernelGGL((attn_decode_split_kernel<D, G, kAttnDirectWaves<G>>), dim3(1, hkv), dim3(kAttnDirectWaves<G> * 64),
+                       0, st, q, k, v, len, max_len, p.tc, 1, sl2, ws, o, o16);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL((attn_decode_split_kernel<D, G, kAttnWaves>), dim3(p.nsplit, hkv), dim3(kAttnWaves * 64), 0, st,
+                     q, k, v, len, max_len, p.tc, p.nsplit, sl2, ws, nullptr, nullptr);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((attn_decode_combine_kernel<D>), dim3(hkv * G), dim3(kMergeThreads), 0, st, ws, p.nsplit, o,
+                     o16);
   return hipGetLastError();
 }
 
@@ -754,22 +788,18 @@ hipError_t launch_attn_prefill(const uint16_t* q, const uint16_t* k, const uint1
   return hipGetLastError();
 }
 
-// Slices: enough workgroups for about two per CU over the KV heads, at
-// least 32 rows each (a multiple of 32), at most kAttnMaxSplits slices, and
-// few enough rows that the G x rows scores fit in 32 KiB of LDS.
-AttnPlan attn_decode_plan(int hkv, int group, int64_t len, int cu_count) {
-  // Short caches: one slice per KV head, which writes the output itself (no
-  // merge launch); a few memory round trips cost less than the second launch.
-  if (len <= kAttnDirectLen) return AttnPlan{static_cast<int>((len + 31) / 32 * 32), 1};
-  const int64_t want = (2 * static_cast<int64_t>(cu_count) + hkv - 1) / hkv;
-  const int64_t tc_max = kAttnScoreFloats / group / 32 * 32;
-  int64_t nsplit = std::min<int64_t>(std::min<int64_t>(want, kAttnMaxSplits), (len + 31) / 32);
-  nsplit = std::max<int64_t>(nsplit, (len + tc_max - 1) / tc_max);
-  nsplit = std::max<int64_t>(nsplit, 1);
-  int64_t tc = (len + nsplit - 1) / nsplit;
-  tc = (tc + 31) / 32 * 32;
-  nsplit = (len + tc - 1) / tc;
-  return AttnPlan{static_cast<int>(tc), static_cast<int>(nsplit)};
+// Slices: short caches (rows x heads x dimensions up to 64 K per KV head) go as
+// one slice per KV head, which writes the output itself: up to there the extra
+// steps of one workgroup cost less than a merge launch (us, one slice / split:
+// 16 / 8 heads of 128: 5.3 / 6.0 at 200 rows, 7.2 / 6.6 at 400; 8 / 8 heads:
+// 5.3 / 6.1 at 400; 32 / 8 heads of 64: 5.7 / 7.0 at 200).  Beyond, about two
+// workgroups per CU over the KV heads, at least 64 rows each (a multiple of
+// 64), at most kAttnMaxSplits slices.
+AttnPlan attn_decode_plan(int hkv, int group, int d, int64_t len, int cu_count) {
+  if (len * group * d <= kAttnDirectWork) return AttnPlan{static_cast<int>(len), 1};
+  const int64_t want = std::min<int64_t>((2 * static_cast<int64_t>(cu_count) + hkv - 1) / hkv, kAttnMaxSplits);
+  const int64_t tc = ((len + want - 1) / want + 63) / 64 * 64;
+  return AttnPlan{static_cast<int>(tc), static_cast<int>((len + tc - 1) / tc)};
 }
 
 size_t attn_decode_workspace_bytes(int32_t hq, int32_t d) {
@@ -780,7 +810,7 @@ hipError_t launch_attn_decode(const uint16_t* q, const uint16_t* k, const uint16
                               int32_t d, int64_t len, int64_t max_len, float scale, float* o, uint16_t* o16,
                               float* ws, int cu_count, hipStream_t st) {
   const int group = hq / hkv;
-  const AttnPlan p = attn_decode_plan(hkv, group, len, cu_count);
+  const AttnPlan p = attn_decode_plan(hkv, group, d, len, cu_count);
   return d == 64 ? launch_decode_d<64>(group, q, k, v, hkv, len, max_len, scale, o, o16, ws, p, st)
                  : launch_decode_d<128>(group, q, k, v, hkv, len, max_len, scale, o, o16, ws, p, st);
 }

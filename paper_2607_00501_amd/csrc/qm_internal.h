@@ -151,11 +151,10 @@ hipError_t launch_gemm_swiglu(int32_t fmt, const uint8_t* qg, const uint16_t* sg
 
 // Decode attention: KV rows per workgroup slice and number of slices.
 constexpr int kAttnMaxSplits = 256;
-constexpr int kAttnScoreFloats = 8192;           // LDS floats for the scores of one slice (32 KiB)
-constexpr int64_t kAttnMaxLen = 262144;          // kAttnMaxSplits x (kAttnScoreFloats / 8 heads)
-constexpr int64_t kAttnDirectLen = 128;          // caches up to this length: one slice, no merge
+constexpr int64_t kAttnMaxLen = 262144;
+constexpr int64_t kAttnDirectWork = 65536;       // rows x heads x head_dim up to this: one slice, no merge
 struct AttnPlan { int tc; int nsplit; };
-AttnPlan attn_decode_plan(int hkv, int group, int64_t len, int cu_count);
+AttnPlan attn_decode_plan(int hkv, int group, int d, int64_t len, int cu_count);
 size_t attn_decode_workspace_bytes(int32_t hq, int32_t d);
 hipError_t launch_attn_decode(const uint16_t* q, const uint16_t* k, const uint16_t* v, int32_t hq, int32_t hkv,
                               int32_t d, int64_t len, int64_t max_len, float scale, float* o, uint16_t* o16,
