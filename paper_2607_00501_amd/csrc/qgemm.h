@@ -118,27 +118,30 @@ __device__ __forceinline__ void vm_wait_live(int live, std::integer_sequence<int
 // every outstanding load (vmcnt 0) before the next use of any loaded
 // register.  The hardware still counts it in vmcnt; the kernel waits for it
 // explicitly (vm_wait), and every later wait the compiler computes stays
-// conservative.
+// conservative.  The s_nop is the wait state gfx9 needs between a scalar write
+// of M0 and an LDS DMA, which the assembler does not add inside inline asm:
+// without it the DMA may take the previous M0 (1 KiB of a tile lands on the piece
+// before).
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
   return static_cast<uint32_t>(reinterpret_cast<size_t>((const void __attribute__((address_space(3)))*)p));
 }
 template <bool NT = false>
 __device__ __forceinline__ void lds_dma16(const void* src, const void* lds_dst) {
   if constexpr (NT)
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off nt" : : "v"(src), "s"(lds_address(lds_dst))
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" : : "v"(src), "s"(lds_address(lds_dst))
                  : "memory", "m0");
   else
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(lds_address(lds_dst))
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(lds_address(lds_dst))
                  : "memory", "m0");
 }
 // 4 bytes per lane, lane l to lds_dst + 4 l.
 template <bool NT = false>
 __device__ __forceinline__ void lds_dma4(const void* src, const void* lds_dst) {
   if constexpr (NT)
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dword %0, off nt" : : "v"(src), "s"(lds_address(lds_dst))
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off nt" : : "v"(src), "s"(lds_address(lds_dst))
                  : "memory", "m0");
   else
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dword %0, off" : : "v"(src), "s"(lds_address(lds_dst))
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" : : "v"(src), "s"(lds_address(lds_dst))
                  : "memory", "m0");
 }
 
