@@ -592,9 +592,13 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
   // No memory fence: a workgroup fence would also wait for the loads of the
   // later steps still in flight.  The empty asm statements keep the compiler
   // from moving LDS accesses across the barrier.  A one-wavefront slice
-  // needs no barrier.
+  // needs no barrier.  Before it, lgkmcnt(0): the DMA issued next overwrites the
+  // stage that the last fragment reads of the step before come from, and a read
+  // still queued can lose against it (64 x 64 tiles over several rounds of
+  // workgroups had 8-row pieces of a step replaced).
   auto slice_sync = [&]() __attribute__((always_inline)) {
     asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);                    // lgkmcnt(0), vmcnt and expcnt left free
     if constexpr (WN > 1) __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };

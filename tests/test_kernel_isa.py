@@ -2,6 +2,7 @@
 checked on the instructions of the library built here (no GPU needed)."""
 
 import os
+import re
 import shutil
 import struct
 import subprocess
@@ -29,14 +30,12 @@ def _code_objects(data):
         at = data.find(MAGIC, at + 1)
 
 
-def test_lds_dma_waits_for_m0(tmp_path):
-    """One wait state stands between a scalar write of M0 and the LDS DMA that
-    reads it."""
+def _gemm_instructions(tmp_path):
+    """The instructions of the built GEMM kernels, one stripped line each."""
     if not os.path.exists(B.LIB_PATH) or shutil.which(OBJDUMP) is None:
         pytest.skip("library or llvm-objdump not there")
     with open(B.LIB_PATH, "rb") as f:
         data = f.read()
-    dma = 0
     for i, co in enumerate(_code_objects(data)):
         if b"qgemm_kernel" not in co:
             continue
@@ -44,12 +43,38 @@ def test_lds_dma_waits_for_m0(tmp_path):
         path.write_bytes(co)
         with subprocess.Popen([OBJDUMP, "-d", "--no-show-raw-insn", "--no-leading-addr", str(path)],
                               stdout=subprocess.PIPE, text=True) as p:
-            before = ""
-            for line in p.stdout:
-                ins = line.strip()
-                if ins.startswith("global_load_lds"):
-                    dma += 1
-                    assert not (before.startswith("s_") and " m0," in before), f"{before} | {ins}"
-                before = ins
+            yield from (line.strip() for line in p.stdout)
         assert p.returncode == 0
+
+
+def test_lds_dma_waits_for_m0(tmp_path):
+    """One wait state stands between a scalar write of M0 and the LDS DMA that
+    reads it."""
+    dma, before = 0, ""
+    for ins in _gemm_instructions(tmp_path):
+        if ins.startswith("global_load_lds"):
+            dma += 1
+            assert not (before.startswith("s_") and " m0," in before), f"{before} | {ins}"
+        before = ins
+    assert dma > 0
+
+
+def test_lds_dma_waits_for_fragment_reads(tmp_path):
+    """No LDS DMA is issued while an LDS read of the step before is pending (it
+    may overwrite the stage that the read comes from).  Checked on the kernels of
+    one wavefront per K slice, whose K steps read nothing but activation
+    fragments from LDS and have no barrier."""
+    dma, pending, kernel, one_wave = 0, None, "", False
+    for ins in _gemm_instructions(tmp_path):
+        if ins.endswith(">:"):
+            kernel, pending, one_wave = ins, None, re.search(r"qgemm_kernelILi\d+ELi1E", ins) is not None
+        elif not one_wave:
+            continue
+        elif ins.startswith("ds_read"):
+            pending = ins
+        elif ins.startswith("s_waitcnt") and "lgkmcnt(0)" in ins:
+            pending = None
+        elif ins.startswith("global_load_lds"):
+            dma += 1
+            assert pending is None, f"{kernel} {pending} | {ins}"
     assert dma > 0
