@@ -29,7 +29,12 @@ hipError_t launch_tile(const QgemmArgs& a, hipStream_t st) {
 // Llama-3.2-1B, Llama-3.2-3B and Qwen3-0.6B shapes and their grouped widths
 // at M = 128, 512, 2048 (K steps of 64):
 //  * 128 x 256 tiles when they give at least 3/4 workgroup per CU;
-//  * else 64 x 256 tiles when they give at least 3/4 per CU;
+//  * else 64 x 256 tiles when they give at least 3/4 per CU; with 2-way split-K
+//    when they give at most one per CU and K has >= 32 steps: two wavefronts per
+//    SIMD in the place of one, so that one's dequantisation and LDS reads run
+//    under the other's MFMAs (us, 1-way / 2-way: Q4 1024 x 6144 -> 4096 63.1 /
+//    60.0, 1900 x 8192 -> 1600 75.9 / 68.1; Q8 2048 x 8192 -> 2048 91.5 / 83.6,
+//    800 x 4096 -> 4096 42.7 / 40.2; at 16 steps 16.6 / 16.6, at 8 11.8 / 12.4);
 //  * else 64 x 128 tiles with 2-way split-K when those give at least 3/4
 //    workgroup per CU and K has >= 16 steps;
 //  * else one 64-column panel per K slice with split-K over as many
@@ -57,7 +62,7 @@ GemmPlan gemm_plan(int64_t m, int64_t n, int64_t k, int cu_count) {
   const int64_t cu = cu_count;
   const int64_t kt = (k / kGroup + 1) / 2;
   if (4 * blocks(128, 4) >= 3 * cu) return GemmPlan{128, 4, 1};
-  if (4 * blocks(64, 4) >= 3 * cu) return GemmPlan{64, 4, 1};
+  if (4 * blocks(64, 4) >= 3 * cu) return GemmPlan{64, 4, blocks(64, 4) <= cu && kt >= 32 ? 2 : 1};
   if (4 * blocks(64, 2) >= 3 * cu && kt >= 16) return GemmPlan{64, 2, 2};
   const int64_t min_steps = kt < 32 ? 4 : 8;
   int wk = 1;
@@ -78,7 +83,7 @@ namespace {
 // The tiles gemm_plan() can choose (QM_GEMM_PLAN may force any of them).
 // Every format instantiates the same tiles.
 #define QM_GEMM_TILES(X) \
-  X(128, 4, 1) X(64, 4, 1) X(64, 2, 2) \
+  X(128, 4, 1) X(64, 4, 1) X(64, 4, 2) X(64, 2, 2) \
   X(64, 1, 1) X(64, 1, 2) X(64, 1, 4) X(64, 1, 8) X(32, 1, 1) X(32, 1, 2) X(32, 1, 4) X(32, 1, 8)
 
 hipError_t launch_args(const QgemmArgs& a, int32_t fmt, int cu_count, hipStream_t st) {
@@ -166,6 +171,7 @@ hipError_t launch_gemm_swiglu(int32_t fmt, const uint8_t* qg, const uint16_t* sg
   auto go = [&](auto ft) -> hipError_t {
     constexpr int F = decltype(ft)::value;
     if (p.bm == 128) return launch_swiglu_tile<128, 4, 1, F>(a, st);
+    if (p.bm == 64 && p.wn == 4 && p.wk == 2) return launch_swiglu_tile<64, 4, 2, F>(a, st);
     if (p.bm == 64 && p.wn == 4) return launch_swiglu_tile<64, 4, 1, F>(a, st);
     return launch_swiglu_tile<64, 2, 2, F>(a, st);
   };

@@ -330,11 +330,13 @@ struct Cfg {
   // when B also goes through LDS, per wavefront and weight matrix the two
   // code chunks and their 2 x 64 scales (Q4 2304 B, Q8 4352 B).  B goes through LDS
   // for multi-wavefront slices whose DEPTH + 1 stages fit in 80 KiB (two
-  // workgroups per CU); otherwise B is loaded into registers.
+  // workgroups per CU; eight-wavefront workgroups, which the registers limit to
+  // one per CU, in 156 KiB); otherwise B is loaded into registers.
   static constexpr int kAStageBytes = WK * BM * kBK * 2;
   static constexpr int kBMatBytes = 2 * kChunkBytes + 256;
   static constexpr int kBWaveBytes = kNB * kBMatBytes;
-  static constexpr bool kBLds = !kFloat && WN > 1 && kSlots * (kAStageBytes + WN * WK * kBWaveBytes) <= 80 * 1024;
+  static constexpr int kLdsCap = (WN * WK <= 4 ? 80 : 156) * 1024;
+  static constexpr bool kBLds = !kFloat && WN > 1 && kSlots * (kAStageBytes + WN * WK * kBWaveBytes) <= kLdsCap;
   static constexpr int kStageBytes = kAStageBytes + (kBLds ? WN * WK * kBWaveBytes : 0);
   // A LDS stages: DEPTH + 1 (A loaded DEPTH steps ahead, like B) when they
   // fit in 48 KiB or B goes through LDS, else 2 (A loaded one step ahead),
