@@ -409,7 +409,8 @@ hipError_t launch_combine(const MoeArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int BMG, int WKG, int BMD, int WKD, int WN, int DG = 2, int DD = 2, bool NT = false, int FMT = QM_Q4_G32>
+template <int BMG, int WKG, int BMD, int WKD, int WNG, int DG = 2, int DD = 2, bool NT = false, int FMT = QM_Q4_G32,
+          int WND = WNG>
 hipError_t launch_moe_tiles(const MoeArgs& a, hipStream_t st) {
   const int64_t A = a.m * a.top_k;
   // Upper bound on the number of (expert, row tile) pairs: sum of
@@ -423,22 +424,22 @@ hipError_t launch_moe_tiles(const MoeArgs& a, hipStream_t st) {
   g.q = a.gq; g.s = a.gs; g.q2 = a.uq; g.s2 = a.us; g.a = a.x; g.h = a.h; g.N = a.inter; g.K = a.hidden;
   // 1-D grids over (row tile, column block) units, rounded up to whole
   // rounds of XCD chunks (the XCD mapping is done in the kernel).
-  auto grid = [&](int bm, int64_t n) {
-    const int64_t ny = (padded_rows(n) + 64 * WN - 1) / (64 * WN);
+  auto grid = [&](int bm, int wn, int64_t n) {
+    const int64_t ny = (padded_rows(n) + 64 * wn - 1) / (64 * wn);
     const int64_t round = static_cast<int64_t>(kXcds) * qg::kMoeChunkTiles * ny;
     const int64_t units = static_cast<int64_t>(tiles(bm)) * ny;
     return dim3(static_cast<unsigned>((units + round - 1) / round * round));
   };
   g.tiles = tiles(BMG);
-  hipLaunchKernelGGL((qgemm_kernel<BMG, WN, WKG, QgMode::kMoeGateUp, DG, NT, FMT>), grid(BMG, a.inter), dim3(WN * WKG * 64), 0,
-                     st, g);
+  hipLaunchKernelGGL((qgemm_kernel<BMG, WNG, WKG, QgMode::kMoeGateUp, DG, NT, FMT>), grid(BMG, WNG, a.inter),
+                     dim3(WNG * WKG * 64), 0, st, g);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // down, scaled by the gate weight and scattered to the assignment slot
   g.q = a.dq; g.s = a.ds; g.q2 = nullptr; g.s2 = nullptr; g.a = a.h; g.yp = a.yp; g.N = a.hidden; g.K = a.inter;
   g.tiles = tiles(BMD);
-  hipLaunchKernelGGL((qgemm_kernel<BMD, WN, WKD, QgMode::kMoeDown, DD, NT, FMT>), grid(BMD, a.hidden), dim3(WN * WKD * 64), 0,
-                     st, g);
+  hipLaunchKernelGGL((qgemm_kernel<BMD, WND, WKD, QgMode::kMoeDown, DD, NT, FMT>), grid(BMD, WND, a.hidden),
+                     dim3(WND * WKD * 64), 0, st, g);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_combine(a, st);
@@ -544,7 +545,6 @@ hipError_t launch_route(const float* logits, int64_t m, int32_t e, int32_t k, in
 }
 
 hipError_t launch_moe(const MoeArgs& a, int cu_count, hipStream_t st) {
-  (void)cu_count;
   // Tuning sweeps only: QM_MOE_PLAN="bm_gate_up,wk_gate_up,bm_down,wk_down,
   // depth_gate_up,depth_down,nontemporal".
   static const std::array<int, 7> forced = [] {
@@ -577,12 +577,28 @@ hipError_t launch_moe(const MoeArgs& a, int cu_count, hipStream_t st) {
   // three launches): 45.9 -> 18.3 at 1 token, 46.8 -> 32.0 at 4, 77.1 -> 61.8 at
   // 16, 86.7 -> 80.0 at 32, 90.8 -> 93.0 at 64; Q3 and Q5 turn at 1.5 rows per
   // expert (Q3 95.8 -> 89.2 at 1, 103.8 -> 113.5 at 2).
+  // 32-row tiles of a product whose 4-panel column blocks would leave CUs without
+  // a workgroup: 2-panel blocks with 2-way split-K, twice the
+  // workgroups with half the chain of K steps.  The lines (us, products and
+  // combine, before / after, at 48 tokens): 32 experts of 1536 -> 1024, top-4 (128
+  // and 192 blocks) Q4 42.1 / 33.6, Q8 48.6 / 42.6; 32 of 1024 -> 512 30.7 / 23.5;
+  // 128 of 1024 -> 256, top-8 (128 blocks, down 4-panel) Q4 32.1 / 27.9.  Narrow
+  // gate/up at 160 blocks (32 of 2048 -> 1280): Q4 51.4 / 48.0 but Q8 62.0 / 65.7;
+  // at 192 (64 of 2048 -> 768) Q4 52.9 / 54.9, Q8 65.3 / 73.7.
   const int64_t rpe = a.m * a.top_k / a.n_experts;
+  const int64_t used = std::min<int64_t>(a.n_experts, a.m * a.top_k);
+  auto blocks = [&](int64_t n) { return used * ((padded_rows(n) + 255) / 256); };
+  const bool narrow_g = 2 * blocks(a.inter) <= cu_count, narrow_d = 4 * blocks(a.hidden) <= 3 * cu_count;
   const bool few = 2 * a.m * a.top_k <= 3 * static_cast<int64_t>(a.n_experts);
   auto plan = [&](auto f) -> hipError_t {
     constexpr int F = decltype(f)::value;
     if (few) return launch_moe_fewrow<2, 4, 2, F>(a, st);
-    if (rpe <= 24) return launch_moe_tiles<32, 1, 32, 1, 4, 2, 2, true, F>(a, st);
+    if (rpe <= 24) {
+      if (narrow_g && narrow_d) return launch_moe_tiles<32, 2, 32, 2, 2, 2, 2, true, F, 2>(a, st);
+      if (narrow_g) return launch_moe_tiles<32, 2, 32, 1, 2, 2, 2, true, F, 4>(a, st);
+      if (narrow_d) return launch_moe_tiles<32, 1, 32, 2, 4, 2, 2, true, F, 2>(a, st);
+      return launch_moe_tiles<32, 1, 32, 1, 4, 2, 2, true, F, 4>(a, st);
+    }
     if constexpr (F == QM_Q5_G32 || F == QM_Q6_G32 || F == QM_Q8_G32) {
       return launch_moe_tiles<32, 1, 64, 1, 4, 2, 2, false, F>(a, st);
     } else {
