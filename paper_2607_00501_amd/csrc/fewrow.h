@@ -149,7 +149,7 @@ __device__ __forceinline__ void body(const QgemmArgs& p) {
   const int wrow = 16 * RT * sub + c;                     // weight row of tile 0 inside the panel
   // Activations: load i of a step takes rows 4i .. 4i + 3, 256 contiguous
   // bytes of each (16-byte piece lane % 16 of row 4i + lane / 16).  Offsets in
-  // 16-byte units (m k / 8 < 2^31).
+  // 16-byte units, 32 bits (the plans check fewrow_addressable).
   const u32x4* xbase = reinterpret_cast<const u32x4*>(p.a);
   uint32_t xoff[XR];
 #pragma unroll

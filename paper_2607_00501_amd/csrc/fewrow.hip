@@ -55,6 +55,7 @@ FewrowPlan fewrow_plan(int32_t fmt, int64_t m, int64_t n, int64_t k, int cu_coun
     std::sscanf(e, "%d,%d,%d", &f.rt, &f.xr, &f.u);
     return f;
   }
+  if (!fewrow_addressable(m, k)) return FewrowPlan{0, 0, 1};
   const int64_t panels = padded_rows(n) / kPanel;
   const bool wide = fmt_bits(fmt) >= 8;
   auto take = [&](int rt, int xr) {
@@ -81,7 +82,8 @@ FewrowPlan fewrow_plan(int32_t fmt, int64_t m, int64_t n, int64_t k, int cu_coun
 // 8.5; the MFMA tiles take 14.2 and 15.6); 32-row blocks also with two per CU
 // (m = 64: 14.8 -> 13.6, tiles 14.9), but not for Q8 and the float formats (Q8:
 // 18.6, tiles 17.2).
-FewrowPlan fewrow_swiglu_plan(int32_t fmt, int64_t m, int64_t n, int cu_count) {
+FewrowPlan fewrow_swiglu_plan(int32_t fmt, int64_t m, int64_t n, int64_t k, int cu_count) {
+  if (!fewrow_addressable(m, k)) return FewrowPlan{0, 0, 1};
   const int64_t panels = padded_rows(n) / kPanel;
   auto groups = [&](int rt, int xr) { return panels * (4 / rt) * ((m + 4 * xr - 1) / (4 * xr)); };
 #define QM_FR(RT, XR) \

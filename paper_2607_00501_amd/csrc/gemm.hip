@@ -165,7 +165,7 @@ hipError_t launch_gemm_swiglu(int32_t fmt, const uint8_t* qg, const uint16_t* sg
   a.a = x; a.M = m; a.K = k; a.N = n; a.h = h;
   a.q = qg; a.s = sg; a.q2 = qu; a.s2 = su;
   a.gq[0] = qg; a.gs[0] = sg; a.gq[1] = qu; a.gs[1] = su;
-  const FewrowPlan f = fewrow_swiglu_plan(fmt, m, n, cu_count);
+  const FewrowPlan f = fewrow_swiglu_plan(fmt, m, n, k, cu_count);
   if (f.rt != 0) return launch_fewrow_swiglu(a, fmt, f, st);
   const GemmPlan p = gemm_plan(m, 2 * padded_rows(n), k, cu_count);
   auto go = [&](auto ft) -> hipError_t {

@@ -544,6 +544,12 @@ hipError_t launch_route(const float* logits, int64_t m, int32_t e, int32_t k, in
   return hipGetLastError();
 }
 
+// At most 1.5 rows per expert in the mean (decode batches), and activations
+// that the kernel can address: x rows for gate/up, h rows for down.
+bool moe_few_rows(int64_t m, int32_t top_k, int64_t n_experts, int64_t hidden, int64_t inter) {
+  return 2 * m * top_k <= 3 * n_experts && fewrow_addressable(m, hidden) && fewrow_addressable(m * top_k, inter);
+}
+
 hipError_t launch_moe(const MoeArgs& a, int cu_count, hipStream_t st) {
   // Tuning sweeps only: QM_MOE_PLAN="bm_gate_up,wk_gate_up,bm_down,wk_down,
   // depth_gate_up,depth_down,nontemporal".
@@ -570,9 +576,9 @@ hipError_t launch_moe(const MoeArgs& a, int cu_count, hipStream_t st) {
   // (their LDS stages do not fit beside two workgroups' A stages), and the
   // two-matrix gate/up tile then holds 64 rows only by spilling: their
   // gate/up tiles stay at 32 rows.
-  // At most 1.5 rows per expert in the mean (decode batches): the few-row
-  // kernel with 32-row sub-panels for gate/up, whole panels for down and 8-row
-  // blocks; the 32 x 256 tiles leave 24 workgroups busy at one token.
+  // Where moe_few_rows() holds: the few-row kernel with 32-row sub-panels for
+  // gate/up, whole panels for down and 8-row blocks; the 32 x 256 tiles leave 24
+  // workgroups busy at one token.
   // Measured on MI355X (128 experts, top-8, 2048 -> 768 -> 2048, Q4, us for the
   // three launches): 45.9 -> 18.3 at 1 token, 46.8 -> 32.0 at 4, 77.1 -> 61.8 at
   // 16, 86.7 -> 80.0 at 32, 90.8 -> 93.0 at 64; Q3 and Q5 turn at 1.5 rows per
@@ -589,7 +595,7 @@ hipError_t launch_moe(const MoeArgs& a, int cu_count, hipStream_t st) {
   const int64_t used = std::min<int64_t>(a.n_experts, a.m * a.top_k);
   auto blocks = [&](int64_t n) { return used * ((padded_rows(n) + 255) / 256); };
   const bool narrow_g = 2 * blocks(a.inter) <= cu_count, narrow_d = 4 * blocks(a.hidden) <= 3 * cu_count;
-  const bool few = 2 * a.m * a.top_k <= 3 * static_cast<int64_t>(a.n_experts);
+  const bool few = moe_few_rows(a.m, a.top_k, a.n_experts, a.hidden, a.inter);
   auto plan = [&](auto f) -> hipError_t {
     constexpr int F = decltype(f)::value;
     if (few) return launch_moe_fewrow<2, 4, 2, F>(a, st);

@@ -256,7 +256,11 @@ bool gemm_plan_instantiated(const GemmPlan& p);   // a prefill GEMM tile exists 
 // workgroup, u steps in flight (rt = 0: take the tiles of gemm_plan).
 struct FewrowPlan { int rt; int xr; int u; };
 FewrowPlan fewrow_plan(int32_t fmt, int64_t m, int64_t n, int64_t k, int cu_count);
-FewrowPlan fewrow_swiglu_plan(int32_t fmt, int64_t m, int64_t n, int cu_count);
+FewrowPlan fewrow_swiglu_plan(int32_t fmt, int64_t m, int64_t n, int64_t k, int cu_count);
+// The few-row kernel keeps activation offsets in 16-byte units as 32 bits.
+constexpr bool fewrow_addressable(int64_t rows, int64_t k) { return rows * (k / 8) <= int64_t(1) << 32; }
+// Whether the expert products of a call take the few-row kernel.
+bool moe_few_rows(int64_t m, int32_t top_k, int64_t n_experts, int64_t hidden, int64_t inter);
 const char* gemm_tile_name(int64_t m, int64_t n);
 const char* moe_tile_name(int64_t rows_per_expert);
 

@@ -1,9 +1,14 @@
 """Shared test helpers: the comparison metric and a test-side construction of
-the device layout written from its definition in include/qmatmul.h."""
+the device layout written from its definition in include/qmatmul.h, and the
+library's launch plans (host functions of sizes, formats and the CU count)."""
+
+import ctypes
+import functools
 
 import numpy as np
 
 from oracle import qmatmul_oracle as O
+from paper_2607_00501_amd import binding as B
 
 
 def rel_err(y, ref) -> float:
@@ -20,6 +25,39 @@ def rel_err(y, ref) -> float:
 
 GEMV_TOL = 2e-3    # fp32 accumulation
 MFMA_TOL = 1e-2    # fp16 MFMA inputs
+
+
+class _Plan(ctypes.Structure):
+    _fields_ = [("a", ctypes.c_int), ("b", ctypes.c_int), ("c", ctypes.c_int)]
+
+
+@functools.cache
+def _plan_fn(symbol, args, restype):
+    fn = getattr(B.lib(), symbol)
+    fn.argtypes = [{"i": ctypes.c_int32, "l": ctypes.c_int64}[c] for c in args]
+    fn.restype = restype
+    return fn
+
+
+def _plan(symbol, args, *values):
+    p = _plan_fn(symbol, args, _Plan)(*values)
+    return p.a, p.b, p.c
+
+
+def fewrow_plan(fmt, m, n, k, cu=256):
+    """(rt, xr, u) of a dense call on the few-row kernel, None on the tiles."""
+    p = _plan("_ZN2qm11fewrow_planEillli", "illli", fmt, m, n, k, cu)
+    return p if p[0] else None
+
+
+def fewrow_swiglu_plan(fmt, m, n, k, cu=256):
+    p = _plan("_ZN2qm18fewrow_swiglu_planEillli", "illli", fmt, m, n, k, cu)
+    return p if p[0] else None
+
+
+def moe_few_rows(m, top_k, experts, hidden, inter):
+    """Whether the expert products of a call take the few-row kernel."""
+    return _plan_fn("_ZN2qm12moe_few_rowsElilll", "lilll", ctypes.c_bool)(m, top_k, experts, hidden, inter)
 
 
 def _nibble_plane(u):
