@@ -69,7 +69,7 @@ FewrowPlan fewrow_plan(int32_t fmt, int64_t m, int64_t n, int64_t k, int cu_coun
   if (take(RT, XR)) return FewrowPlan{RT, XR, RT <= 2 && k >= 4096 ? 2 : 1};
   QM_FEWROW_TILES(QM_FR)
 #undef QM_FR
-  if (m <= 32 && panels > cu_count) return FewrowPlan{4, m <= 8 ? 2 : m <= 16 ? 4 : 8, 1};
+  if (m <= 32 && panels > cu_count && fewrow_launchable(panels)) return FewrowPlan{4, m <= 8 ? 2 : m <= 16 ? 4 : 8, 1};
   return FewrowPlan{0, 0, 1};
 }
 

@@ -544,10 +544,15 @@ hipError_t launch_route(const float* logits, int64_t m, int32_t e, int32_t k, in
   return hipGetLastError();
 }
 
-// At most 1.5 rows per expert in the mean (decode batches), and activations
-// that the kernel can address: x rows for gate/up, h rows for down.
+// At most 1.5 rows per expert in the mean (decode batches) and grids that can
+// be launched: at most a row block per assignment, two sub-panels of a gate/up
+// panel, one of a down panel, rounded up over the XCDs.  (Such activations, x
+// rows for gate/up and h rows for down, are fewrow_addressable: A times hidden
+// or inter is below 2^29.)
 bool moe_few_rows(int64_t m, int32_t top_k, int64_t n_experts, int64_t hidden, int64_t inter) {
-  return 2 * m * top_k <= 3 * n_experts && fewrow_addressable(m, hidden) && fewrow_addressable(m * top_k, inter);
+  const int64_t A = m * top_k;
+  return 2 * A <= 3 * n_experts && fewrow_launchable(A * (padded_rows(inter) / kPanel) * 2 + 2 * kXcds) &&
+         fewrow_launchable(A * (padded_rows(hidden) / kPanel) + kXcds);
 }
 
 hipError_t launch_moe(const MoeArgs& a, int cu_count, hipStream_t st) {

@@ -259,6 +259,9 @@ FewrowPlan fewrow_plan(int32_t fmt, int64_t m, int64_t n, int64_t k, int cu_coun
 FewrowPlan fewrow_swiglu_plan(int32_t fmt, int64_t m, int64_t n, int64_t k, int cu_count);
 // The few-row kernel keeps activation offsets in 16-byte units as 32 bits.
 constexpr bool fewrow_addressable(int64_t rows, int64_t k) { return rows * (k / 8) <= int64_t(1) << 32; }
+// A launch takes fewer than 2^32 threads per grid dimension; the few-row kernel
+// has 512 per workgroup, up to 32 times the tiles' count per weight row.
+constexpr bool fewrow_launchable(int64_t groups) { return groups < int64_t(1) << 23; }
 // Whether the expert products of a call take the few-row kernel.
 bool moe_few_rows(int64_t m, int32_t top_k, int64_t n_experts, int64_t hidden, int64_t inter);
 const char* gemm_tile_name(int64_t m, int64_t n);

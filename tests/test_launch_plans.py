@@ -21,6 +21,17 @@ def test_fewrow_addresses_its_activations(m, k):
 
 def test_moe_few_rows_addresses_its_activations():
     assert moe_few_rows(16, 8, 128, 2048, 768) and not moe_few_rows(25, 8, 128, 2048, 768)
-    assert moe_few_rows(16, 1, 64, (1 << 31) - 32, 64) and not moe_few_rows(17, 1, 64, (1 << 31) - 32, 64)
-    # the down product reads a row per assignment
-    assert moe_few_rows(4, 4, 64, 64, (1 << 31) - 32) and not moe_few_rows(5, 4, 64, 64, (1 << 31) - 32)
+    for m, top_k, experts, hidden, inter in [(1024, 1, 1024, 1 << 25, 64), (16, 4, 128, 64, 1 << 29)]:
+        assert m * top_k * max(hidden, inter) // 8 >= 1 << 32 and not moe_few_rows(m, top_k, experts, hidden, inter)
+
+
+# 512 threads per workgroup, fewer than 2^32 per grid dimension: 2^23 workgroups
+# are too many.
+def test_fewrow_grids_can_be_launched():
+    for m in (2, 16, 32):
+        assert fewrow_plan(B.Q4_G32, m, 64 * ((1 << 23) - 1), 32) == (4, max(2, m // 4), 1)
+        for n in (64 << 23, (64 << 23) - 63, 1 << 30):
+            assert fewrow_plan(B.Q4_G32, m, n, 32) is None
+    # gate/up: two sub-panels of every panel and assignment; down: one
+    assert moe_few_rows(1, 8, 1024, 32, 16 << 20) and not moe_few_rows(1, 8, 1024, 32, 32 << 20)
+    assert moe_few_rows(1, 8, 1024, (64 << 20) - 640, 32) and not moe_few_rows(1, 8, 1024, 64 << 20, 32)
