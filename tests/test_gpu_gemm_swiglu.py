@@ -68,3 +68,26 @@ def test_swiglu_gemm_extreme_gates():
     ref = (O.silu(O.gemm(*g, O.F16, x)) * O.gemm(*u, O.F16, x))
     ok = np.abs(ref) < 60000
     assert ok.mean() > 0.5 and np.abs(y - ref)[ok].max() <= MFMA_TOL * np.abs(ref[ok]).max()
+
+
+@pytest.mark.parametrize("m", [1, 16, 130, 2048])    # the GEMV, two few-row tiles, a GEMM tile
+@pytest.mark.parametrize("lo,hi,scale", [(-20, -8, 15000.0), (-8, 0, 64.0), (0, 20, 1.0)])
+def test_swiglu_gemm_rounds_the_exact_value(m, lo, hi, scale):
+    """One fp32 evaluation and one fp16 rounding: with exact G and U the result
+    lies within half an fp16 ulp and the fp32 error of silu(G) * U.  That error
+    is at most 2.5 ulp of 2^-23: 1 for the exponential, 0.5 each for the sum, the
+    quotient and the product."""
+    n, k = 512, 32
+    rng = np.random.default_rng(m + lo + 20)
+    gates = rng.uniform(lo, hi, m).astype(np.float16)
+    ups = (scale * rng.uniform(1, 4, n)).astype(np.float16)
+    x = np.zeros((m, k), np.float16)
+    x[:, 0], x[:, 1] = gates, 1
+    wg, wu = np.zeros((n, k), np.float32), np.zeros((n, k), np.float32)
+    wg[:, 0], wu[:, 1] = 1, ups
+    dev = [B.qm_repack(B.qm_quantise(torch.from_numpy(w).cuda(), B.F16), B.LAYOUT_DEVICE) for w in (wg, wu)]
+    y = B.qmatmul_gemm_swiglu_f16(*dev, torch.from_numpy(x).cuda()).cpu().numpy().astype(np.float64)
+    g = gates.astype(np.float64)[:, None]
+    exact = g / (1 + np.exp(-g)) * ups.astype(np.float64)
+    half_ulp = np.exp2(np.maximum(np.floor(np.log2(np.maximum(np.abs(exact), 1e-30))), -14) - 11)
+    assert np.all(np.abs(y - exact) <= half_ulp + 2.5 * 2.0 ** -23 * np.abs(exact))
