@@ -387,8 +387,12 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
   const int64_t K = p.K, N = p.N;
   const int G = static_cast<int>(K / kGroup);
   const int KT = (G + 1) / 2;
-  const int KTs = (KT + WK - 1) / WK;                      // K steps per slice
-  const int kt0 = wk * KTs;
+  // K steps of the slices differ by at most one, the longer ones last, so that
+  // only the last step of a slice can be empty or (K not a multiple of 64, last
+  // slice) half full.  All slices run KTs steps, which share their barriers.
+  const int KTs = (KT + WK - 1) / WK, longer = KT % WK;
+  const int my_steps = KT / WK + (wk >= WK - longer ? 1 : 0);
+  const int kt0 = wk * (KT / WK) + max(0, wk - (WK - longer));
   const int64_t npad = padded_rows(N);
 
   // Rows of this workgroup.
@@ -596,12 +600,6 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
         }
       }
   };
-  // Scale validity of step t's chunk c, applied when the step is consumed
-  // (a select at load time would wait for the load to land).
-  auto scale_ok = [&](int t, int c) __attribute__((always_inline)) {
-    const int kt = kt0 + t;
-    return cols_ok && 2 * kt + c < G && kt < KT;
-  };
   // The A stages of a K slice are written (by LDS DMA) and read only by the
   // slice's WN wavefronts.  Each wavefront first waits for its own DMA of the
   // step (wait_a); a plain s_barrier then publishes every wavefront's part.
@@ -631,7 +629,7 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
   // Issue order: the prologue takes A of steps 0 .. AD-1 and B of steps
   // 0 .. DEPTH-1 (step q's A before its B); step s then issues A of step
   // s + AD and B of step s + DEPTH, A first, also past the last step
-  // (clamped addresses, zero scales, stages never read).  LDS DMA is never
+  // (clamped addresses, stages never read).  LDS DMA is never
   // dropped, so with B through LDS the count of loads issued after A of
   // step t is the same at every step, and so it is inside the main loop,
   // where every register load has a consumer (the next iteration).  In the
@@ -679,9 +677,12 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
   // One K step t: register slot / LDS stage sl = t % (DEPTH + 1) holds step
   // t's operands, the slots of steps t+1 .. t+DEPTH-1 are in flight, and the
   // slot of step t-1 is refilled with step t+DEPTH once every wavefront of
-  // the slice is past step t-1 (the barrier at the top of the step).
+  // the slice is past step t-1 (the barrier at the top of the step).  tail: the
+  // last step of the slice may lie past K or its second half may; those products
+  // are left out, as their clamped activations may be infinite.
   auto step = [&](auto slot, int t, auto tail) __attribute__((always_inline)) {
     constexpr int sl = decltype(slot)::value;
+    constexpr bool kTail = decltype(tail)::value;
     using Refill = std::integral_constant<int, (sl + DEPTH) % NS>;
     wait_a(t, tail);
     slice_sync();
@@ -695,7 +696,6 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
     for (int j = 0; j < (C::kFloat ? 0 : NB); ++j)
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
-        const bool ok = scale_ok(t, c);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           if constexpr (PL) {
@@ -722,7 +722,6 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
             // Bit planes hold the lane's 16 codes at bits 8h.. and 16 + 8h..
             if constexpr (FMT == QM_Q5_G32) w[2] >>= 8 * lh;
             if constexpr (FMT == QM_Q3_G32) w[1] >>= 8 * lh;
-            sv = ok ? sv : 0u;
             const _Float16 f = __builtin_bit_cast(_Float16, static_cast<uint16_t>(sv));
             sc[j][c][h] = half2v{f, f};
 #pragma unroll
@@ -740,7 +739,6 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
             d = rb[sl][j][c][h];
             sv = rs[sl][j][c][h];
           }
-          sv = ok ? sv : 0u;
           const _Float16 f = __builtin_bit_cast(_Float16, static_cast<uint16_t>(sv));
           sc[j][c][h] = half2v{f, f};
 #pragma unroll
@@ -750,10 +748,7 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
     auto dequant = [&](int j, int h, int ks) __attribute__((always_inline)) {
       const int c = ks >> 1, s = ks & 1;
       if constexpr (C::kFloat) {
-        // Past the last K step (or a padded panel) the clamped quarter is
-        // replaced by zeros: float weights carry no scale to zero it.
-        const u32x4 z = {0u, 0u, 0u, 0u};
-        const u32x4 v = scale_ok(t, c) ? rf[C::kFloat ? sl : 0][j][c][h][s] : z;
+        const u32x4 v = rf[C::kFloat ? sl : 0][j][c][h][s];
         if constexpr (FMT == QM_F16) {
           return __builtin_bit_cast(half8v, v);
         } else {
@@ -779,6 +774,7 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
     __builtin_amdgcn_sched_barrier(0);
     load_b(Refill{}, t + DEPTH);                           // B, DEPTH steps ahead
     __builtin_amdgcn_sched_barrier(0);                               // keep the loads at the top
+    if (kTail && WK > 1 && t >= my_steps) return;
     const char* At = a_tile(a_stage(slot, t));
     // Software pipeline over the four 16-deep substeps: the A fragments and
     // the dequantised B fragments of substep ks+1 are produced while the
@@ -794,6 +790,7 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
     }
 #pragma unroll
     for (int ks = 0; ks < kBK / 16; ++ks) {
+      if (kTail && ks == 2 && 2 * (kt0 + t) + 1 >= G) break;
       const int cur = ks & 1, nxt = cur ^ 1;
       if (ks + 1 < kBK / 16) {
 #pragma unroll
@@ -829,11 +826,12 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
   }(std::make_integer_sequence<int, DEPTH>{});
   using Slots = std::make_integer_sequence<int, NS>;
   int t = 0;
-  for (; t + NS <= KTs; t += NS) {
+  for (; t + NS < KTs; t += NS) {
     [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
       (step(std::integral_constant<int, I>{}, t + I, std::false_type{}), ...);
     }(Slots{});
   }
+  // The last 1 .. NS steps.
   [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
     ((t + I < KTs ? step(std::integral_constant<int, I>{}, t + I, std::true_type{}) : void()), ...);
   }(Slots{});

@@ -55,6 +55,11 @@ def fewrow_swiglu_plan(fmt, m, n, k, cu=256):
     return p if p[0] else None
 
 
+def gemm_plan(m, n, k, cu=256):
+    """(rows, panels, K slices) of the MFMA tile of a dense call not on the few-row kernel."""
+    return _plan("_ZN2qm9gemm_planEllli", "llli", m, n, k, cu)
+
+
 def moe_few_rows(m, top_k, experts, hidden, inter):
     """Whether the expert products of a call take the few-row kernel."""
     return _plan_fn("_ZN2qm12moe_few_rowsElilll", "lilll", ctypes.c_bool)(m, top_k, experts, hidden, inter)

@@ -53,8 +53,8 @@ def test_gemm_large_ragged_sampled():
 
 def test_gemm_two_panel_split_k_ragged_sampled():
     """A shape the 64 x 128 two-way split-K tile takes: 500 rows, 3000
-    columns (a half-filled last panel pair), K = 2080 (33 K steps: the second
-    slice has one step past the end).  Sampled rows and columns."""
+    columns (a half-filled last panel pair), K = 2080 (33 K steps: the first
+    slice is one step short).  Sampled rows and columns."""
     m, n, k = 500, 3000, 2080
     w = inputs.weights_np(inputs.seed_for(3, n, "up", 2), (n, k))
     x = inputs.activations_np(inputs.seed_for(3, m, "x", 2), (m, k))

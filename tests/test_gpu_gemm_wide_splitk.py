@@ -1,5 +1,5 @@
 """GPU parity of the 64 x 256 tiles with 2-way split-K: ragged rows, a last
-column block with one panel short, a K whose second slice is a step short, every
+column block with one panel short, a K whose first slice is a step short, every
 format; dense and with the SwiGLU epilogue."""
 
 import numpy as np
