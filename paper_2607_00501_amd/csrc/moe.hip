@@ -544,15 +544,32 @@ hipError_t launch_route(const float* logits, int64_t m, int32_t e, int32_t k, in
   return hipGetLastError();
 }
 
-// At most 1.5 rows per expert in the mean (decode batches) and grids that can
-// be launched: at most a row block per assignment, two sub-panels of a gate/up
-// panel, one of a down panel, rounded up over the XCDs.  (Such activations, x
-// rows for gate/up and h rows for down, are fewrow_addressable: A times hidden
-// or inter is below 2^29.)
-bool moe_few_rows(int64_t m, int32_t top_k, int64_t n_experts, int64_t hidden, int64_t inter) {
+// Where the expert products take the few-row kernel: at most 1.5 rows per
+// expert in the mean (decode batches); grids that can be launched (at most a row
+// block per assignment, two sub-panels of a gate/up panel, one of a down panel,
+// rounded up over the XCDs; such activations, x rows for gate/up and h rows for
+// down, are fewrow_addressable, as A times hidden or inter is below 2^29); and
+// not too many workgroups for the work in them.  A workgroup costs some time
+// whatever its K (8 wavefronts share K / 128 steps, then add their sums): about
+// A (2 inter + hidden) / 64 of them lose against the tiles, unless K is long
+// enough that their faster products make up for it (inter x hidden / 550); on
+// the other side the tiles launch E (inter + hidden) / 256 workgroups, most of
+// them empty.  Fitted to 1,140 layers of 32 to 1,024 experts, 512 x 256 to 4096 x
+// 1536, 1/8 to 1.5 rows per expert (us for the three launches, few-row / tiles):
+// 256 experts, top-8, 1024 -> 512, 48 tokens Q4 74 / 55, Q8 110 / 76; 24 tokens
+// 49 / 48 and 74 / 67, 8 tokens 28 / 27 and 37 / 34; 1,024, top-16, 512 -> 256, 96
+// tokens 228 / 83 and 324 / 117, 8 tokens 43 / 59 and 46 / 72; 128, top-8, 2048 ->
+// 768, 24 tokens 73 / 83 and 105 / 110.  The rule is within 1% of the better one
+// in the mean, 25% at most (Q6, 512 experts, 1024 -> 512, 16 tokens: 73 / 58).
+bool moe_few_rows(int32_t fmt, int64_t m, int32_t top_k, int64_t n_experts, int64_t hidden, int64_t inter,
+                  int cu_count) {
   const int64_t A = m * top_k;
-  return 2 * A <= 3 * n_experts && fewrow_launchable(A * (padded_rows(inter) / kPanel) * 2 + 2 * kXcds) &&
-         fewrow_launchable(A * (padded_rows(hidden) / kPanel) + kXcds);
+  if (2 * A > 3 * n_experts || !fewrow_launchable(A * (padded_rows(inter) / kPanel) * 2 + 2 * kXcds) ||
+      !fewrow_launchable(A * (padded_rows(hidden) / kPanel) + kXcds))
+    return false;
+  const int64_t per_2cu = fmt == QM_Q8_G32 ? 11 : fmt == QM_Q4_G32 || fmt == QM_Q6_G32 ? 17 : 14;   // workgroups
+  return A * (2 * inter + hidden - inter * hidden / 550) <=
+         32 * per_2cu * cu_count + n_experts * (inter + hidden) / 32;
 }
 
 hipError_t launch_moe(const MoeArgs& a, int cu_count, hipStream_t st) {
@@ -600,7 +617,7 @@ hipError_t launch_moe(const MoeArgs& a, int cu_count, hipStream_t st) {
   const int64_t used = std::min<int64_t>(a.n_experts, a.m * a.top_k);
   auto blocks = [&](int64_t n) { return used * ((padded_rows(n) + 255) / 256); };
   const bool narrow_g = 2 * blocks(a.inter) <= cu_count, narrow_d = 4 * blocks(a.hidden) <= 3 * cu_count;
-  const bool few = moe_few_rows(a.m, a.top_k, a.n_experts, a.hidden, a.inter);
+  const bool few = moe_few_rows(a.format, a.m, a.top_k, a.n_experts, a.hidden, a.inter, cu_count);
   auto plan = [&](auto f) -> hipError_t {
     constexpr int F = decltype(f)::value;
     if (few) return launch_moe_fewrow<2, 4, 2, F>(a, st);

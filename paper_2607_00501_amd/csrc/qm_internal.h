@@ -263,7 +263,8 @@ constexpr bool fewrow_addressable(int64_t rows, int64_t k) { return rows * (k / 
 // has 512 per workgroup, up to 32 times the tiles' count per weight row.
 constexpr bool fewrow_launchable(int64_t groups) { return groups < int64_t(1) << 23; }
 // Whether the expert products of a call take the few-row kernel.
-bool moe_few_rows(int64_t m, int32_t top_k, int64_t n_experts, int64_t hidden, int64_t inter);
+bool moe_few_rows(int32_t fmt, int64_t m, int32_t top_k, int64_t n_experts, int64_t hidden, int64_t inter,
+                  int cu_count);
 const char* gemm_tile_name(int64_t m, int64_t n);
 const char* moe_tile_name(int64_t rows_per_expert);
 

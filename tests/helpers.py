@@ -60,9 +60,9 @@ def gemm_plan(m, n, k, cu=256):
     return _plan("_ZN2qm9gemm_planEllli", "llli", m, n, k, cu)
 
 
-def moe_few_rows(m, top_k, experts, hidden, inter):
+def moe_few_rows(fmt, m, top_k, experts, hidden, inter, cu=256):
     """Whether the expert products of a call take the few-row kernel."""
-    return _plan_fn("_ZN2qm12moe_few_rowsElilll", "lilll", ctypes.c_bool)(m, top_k, experts, hidden, inter)
+    return _plan_fn("_ZN2qm12moe_few_rowsEilillli", "ilillli", ctypes.c_bool)(fmt, m, top_k, experts, hidden, inter, cu)
 
 
 def _nibble_plane(u):

@@ -20,9 +20,18 @@ def test_fewrow_addresses_its_activations(m, k):
 
 
 def test_moe_few_rows_addresses_its_activations():
-    assert moe_few_rows(16, 8, 128, 2048, 768) and not moe_few_rows(25, 8, 128, 2048, 768)
     for m, top_k, experts, hidden, inter in [(1024, 1, 1024, 1 << 25, 64), (16, 4, 128, 64, 1 << 29)]:
-        assert m * top_k * max(hidden, inter) // 8 >= 1 << 32 and not moe_few_rows(m, top_k, experts, hidden, inter)
+        assert m * top_k * max(hidden, inter) // 8 >= 1 << 32
+        assert not moe_few_rows(B.Q4_G32, m, top_k, experts, hidden, inter)
+
+
+@pytest.mark.parametrize("fmt,few,many", [(B.Q4_G32, 9, 40), (B.Q8_G32, 8, 24), (B.Q3_G32, 8, 24)])
+def test_moe_few_rows_leaves_many_short_products_to_the_tiles(fmt, few, many):
+    """256 and 1,024 small experts: a few tokens only; large matrices up to 1.5
+    rows per expert."""
+    assert moe_few_rows(fmt, few, 8, 256, 1024, 512) and not moe_few_rows(fmt, many, 8, 256, 1024, 512)
+    assert moe_few_rows(fmt, 4, 16, 1024, 512, 256) and not moe_few_rows(fmt, many, 16, 1024, 512, 256)
+    assert moe_few_rows(fmt, 24, 8, 128, 4096, 1536) and not moe_few_rows(fmt, 25, 8, 128, 4096, 1536)
 
 
 # 512 threads per workgroup, fewer than 2^32 per grid dimension: 2^23 workgroups
@@ -33,5 +42,6 @@ def test_fewrow_grids_can_be_launched():
         for n in (64 << 23, (64 << 23) - 63, 1 << 30):
             assert fewrow_plan(B.Q4_G32, m, n, 32) is None
     # gate/up: two sub-panels of every panel and assignment; down: one
-    assert moe_few_rows(1, 8, 1024, 32, 16 << 20) and not moe_few_rows(1, 8, 1024, 32, 32 << 20)
-    assert moe_few_rows(1, 8, 1024, (64 << 20) - 640, 32) and not moe_few_rows(1, 8, 1024, 64 << 20, 32)
+    large = lambda hidden, inter: moe_few_rows(B.Q4_G32, 1, 8, 1024, hidden, inter)
+    assert large(1024, 16 << 20) and not large(1024, 32 << 20)
+    assert large((64 << 20) - 640, 1024) and not large(64 << 20, 1024)
