@@ -45,9 +45,16 @@ hipError_t launch_fmt(const QgemmArgs& a, const FewrowPlan& f, hipStream_t st) {
 // m = 17, n = 4785: 12.5 vs 14.0), beyond 128 rows (Q4 1344 -> 1577 at m = 307:
 // 7.9 vs 8.6), XR = 8 at long K (Q4 8192 -> 3072 at m = 128: 17.3 vs 18.1) and
 // for Q8, F16 and BF16, whose weight registers are twice as many or more (F16
-// 2048 -> 3072 at m = 64: 8.0 vs 8.8).  Matrices with more panels than CUs take
-// whole panels up to 32 rows.  Two steps in flight help from K = 4096 (8192 ->
-// 3072 at m = 8: 9.2 -> 7.8) and cost up to 6% at K = 1024.
+// 2048 -> 3072 at m = 64: 8.0 vs 8.8).  RT = 1 and 2 need no such line: few
+// panels leave most of the chip idle whatever the tile, so they win as far as
+// their grid fits, up to 2,048 rows of one panel (312 shapes of 256 and more rows
+// in all formats: 1.14 to 2.4 x; Q4 2048 -> 64 at m = 1,024 3.8 vs 7.2, 8192 -> 64
+// 12.8 vs 15.9, 2048 -> 256 at m = 512 4.6 vs 7.3).  Matrices with more panels
+// than CUs take whole panels up to 16 rows, and up to 32 from K = 1024: with
+// fewer K steps than wavefronts XR = 8 loses (K = 512, m = 24: 65,536 columns Q4
+// 15.9 vs 15.5, Q8 18.3 vs 17.1, 151,936 34 vs 31 and 39 vs 33).  Two steps in
+// flight help from K = 4096 (8192 -> 3072 at m = 8: 9.2 -> 7.8) and cost up to 6%
+// at K = 1024.
 FewrowPlan fewrow_plan(int32_t fmt, int64_t m, int64_t n, int64_t k, int cu_count) {
   // Tuning sweeps only: QM_FEWROW_PLAN="rt,xr,u" forces the plan (rt = 0: none).
   if (const char* e = tuning_override("QM_FEWROW_PLAN")) {
@@ -69,7 +76,8 @@ FewrowPlan fewrow_plan(int32_t fmt, int64_t m, int64_t n, int64_t k, int cu_coun
   if (take(RT, XR)) return FewrowPlan{RT, XR, RT <= 2 && k >= 4096 ? 2 : 1};
   QM_FEWROW_TILES(QM_FR)
 #undef QM_FR
-  if (m <= 32 && panels > cu_count && fewrow_launchable(panels)) return FewrowPlan{4, m <= 8 ? 2 : m <= 16 ? 4 : 8, 1};
+  if (m <= (k >= 1024 ? 32 : 16) && panels > cu_count && fewrow_launchable(panels))
+    return FewrowPlan{4, m <= 8 ? 2 : m <= 16 ? 4 : 8, 1};
   return FewrowPlan{0, 0, 1};
 }
 

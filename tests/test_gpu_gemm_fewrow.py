@@ -9,7 +9,7 @@ import torch
 from oracle import qmatmul_oracle as O
 from paper_2607_00501_amd import binding as B
 from paper_2607_00501_amd import inputs
-from tests.helpers import MFMA_TOL, rel_err
+from tests.helpers import MFMA_TOL, fewrow_plan, rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -34,13 +34,26 @@ def _case(seed, n, k, fmt):
     (77, 3072, 192),       # whole panels (the wide formats take other tiles)
     (128, 3072, 128),      # 32-row blocks of whole panels
     (5, 16448, 96),        # more panels than CUs
-    (31, 16448, 64),
+    (31, 16448, 64),       # as many, K too short for 32 rows: the tiles
 ])
 def test_fewrow_parity(fmt, m, n, k):
     (packed, scales), w = _case(7 * m + k, n, k, fmt)
     x = inputs.activations_np(11 * m + n, (m, k))
     y = B.qmatmul_gemm(w, torch.from_numpy(x).cuda(), out=torch.full((m, n), float("nan"), device="cuda"))
     assert rel_err(y.cpu().numpy(), O.gemm(packed, scales, fmt[0], x)) <= MFMA_TOL
+
+
+@pytest.mark.parametrize("fmt", FORMATS, ids=lambda f: str(f[1]))
+def test_fewrow_wide_matrix_sampled(fmt):
+    """32-row blocks of more panels than CUs, K with a partial last step."""
+    m, n, k = 29, 16440, 1056
+    assert fewrow_plan(fmt[1], m, n, k) == (4, 8, 1)
+    w, x = inputs.weights_np(51, (n, k)), inputs.activations_np(52, (m, k))
+    dev = B.qm_repack(B.qm_quantise(torch.from_numpy(w).cuda(), fmt[1]), B.LAYOUT_DEVICE)
+    y = B.qmatmul_gemm(dev, torch.from_numpy(x).cuda()).cpu().numpy()
+    cols = np.unique(np.concatenate([np.random.default_rng(53).choice(n, 300, replace=False), [0, 63, 64, n - 1]]))
+    q, s = O.quantise(w[cols], fmt[0])
+    assert rel_err(y[:, cols], O.gemm(O.pack(q, fmt[0]), s, fmt[0], x)) <= MFMA_TOL
 
 
 def test_fewrow_group_and_unaligned_output():

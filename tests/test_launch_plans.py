@@ -37,11 +37,19 @@ def test_moe_few_rows_leaves_many_short_products_to_the_tiles(fmt, few, many):
 # 512 threads per workgroup, fewer than 2^32 per grid dimension: 2^23 workgroups
 # are too many.
 def test_fewrow_grids_can_be_launched():
-    for m in (2, 16, 32):
-        assert fewrow_plan(B.Q4_G32, m, 64 * ((1 << 23) - 1), 32) == (4, max(2, m // 4), 1)
+    for m, k in ((2, 32), (16, 32), (32, 1024)):
+        assert fewrow_plan(B.Q4_G32, m, 64 * ((1 << 23) - 1), k) == (4, max(2, m // 4), 1)
         for n in (64 << 23, (64 << 23) - 63, 1 << 30):
-            assert fewrow_plan(B.Q4_G32, m, n, 32) is None
+            assert fewrow_plan(B.Q4_G32, m, n, k) is None
     # gate/up: two sub-panels of every panel and assignment; down: one
     large = lambda hidden, inter: moe_few_rows(B.Q4_G32, 1, 8, 1024, hidden, inter)
     assert large(1024, 16 << 20) and not large(1024, 32 << 20)
     assert large((64 << 20) - 640, 1024) and not large(64 << 20, 1024)
+
+
+def test_fewrow_leaves_short_k_on_wide_matrices_to_the_tiles():
+    """More panels than CUs: up to 16 rows at any K, up to 32 from K = 1024."""
+    for fmt in (B.Q4_G32, B.Q8_G32, B.F16):
+        for n in (16448, 151936):
+            assert fewrow_plan(fmt, 16, n, 512) == (4, 4, 1) and fewrow_plan(fmt, 17, n, 992) is None
+            assert fewrow_plan(fmt, 32, n, 1024) == (4, 8, 1) and fewrow_plan(fmt, 33, n, 1024) is None
