@@ -405,8 +405,10 @@ qm_status qattn_decode_workspace_bytes(int32_t n_q_heads, int32_t head_dim, size
  * v_cache, workspace 16-byte aligned; workspace of at least
  * qattn_decode_workspace_bytes() bytes (caller-owned scratch, contents not
  * preserved).  Scores and sums in fp32, split over the cache length and
- * merged exactly as online softmax does.  Two kernel launches (one, with no
- * merge, when len <= 128); deterministic. */
+ * merged exactly as online softmax does (a row whose weight is below 2^-126 of
+ * the largest counts nothing).  Two kernel launches (one, with no merge, when
+ * len <= 128 or len x query heads per KV head x head_dim <= 65536);
+ * deterministic. */
 qm_status qattn_decode(const uint16_t* q, const uint16_t* k_cache, const uint16_t* v_cache, int32_t n_q_heads,
                        int32_t n_kv_heads, int32_t head_dim, int64_t len, int64_t max_len, float scale, float* o,
                        void* workspace, size_t ws_bytes, void* stream);

@@ -198,8 +198,8 @@ __global__ __launch_bounds__(WAVES * 64) void attn_decode_split_kernel(
     }
   }
   // The row groups of the wavefront, then the wavefronts.  V rows that were
-  // read clamped carry weight 0 (an infinite V there gives NaN, as the last
-  // row itself does).
+  // read clamped carry weight 0 (an infinity in the last row's V becomes NaN
+  // there).
 #pragma unroll
   for (int j = 0; j < G; ++j) {
     const float mw = across_groups<LPR>(m[j], [](float a, float b) { return fmaxf(a, b); });
@@ -788,15 +788,17 @@ hipError_t launch_attn_prefill(const uint16_t* q, const uint16_t* k, const uint1
   return hipGetLastError();
 }
 
-// Slices: short caches (rows x heads x dimensions up to 64 K per KV head) go as
-// one slice per KV head, which writes the output itself: up to there the extra
-// steps of one workgroup cost less than a merge launch (us, one slice / split:
-// 16 / 8 heads of 128: 5.3 / 6.0 at 200 rows, 7.2 / 6.6 at 400; 8 / 8 heads:
-// 5.3 / 6.1 at 400; 32 / 8 heads of 64: 5.7 / 7.0 at 200).  Beyond, about two
-// workgroups per CU over the KV heads, at least 64 rows each (a multiple of
-// 64), at most kAttnMaxSplits slices.
+// Slices: short caches go as one slice per KV head, which writes the output
+// itself: the extra steps of one workgroup cost less than a merge launch.  Rows x
+// heads x dimensions up to 64 K per KV head, and any cache of up to 128 rows (us,
+// one slice / split: 16 / 8 heads of 128: 5.9 / 6.7 at 256 rows, 7.2 / 6.6 at 400;
+// 8 / 8 heads of 64: 6.1 / 6.4 at 1,024; 32 / 8 heads of 64: 6.1 / 7.4 at 256; 48 / 8
+// heads of 128: 7.3 / 8.8 at 96, 8.5 / 9.0 at 128; 64 / 8: 10.3 / 10.1 at 128; with
+// one or two KV heads of one query head up to 5% the other way, 5.9 / 5.6 at 512
+// rows of 128).  Beyond, about two workgroups per CU over the KV heads, at least 64
+// rows each (a multiple of 64), at most kAttnMaxSplits slices.
 AttnPlan attn_decode_plan(int hkv, int group, int d, int64_t len, int cu_count) {
-  if (len * group * d <= kAttnDirectWork) return AttnPlan{static_cast<int>(len), 1};
+  if (len <= kAttnDirectLen || len * group * d <= kAttnDirectWork) return AttnPlan{static_cast<int>(len), 1};
   const int64_t want = std::min<int64_t>((2 * static_cast<int64_t>(cu_count) + hkv - 1) / hkv, kAttnMaxSplits);
   const int64_t tc = ((len + want - 1) / want + 63) / 64 * 64;
   return AttnPlan{static_cast<int>(tc), static_cast<int>((len + tc - 1) / tc)};

@@ -152,7 +152,8 @@ hipError_t launch_gemm_swiglu(int32_t fmt, const uint8_t* qg, const uint16_t* sg
 // Decode attention: KV rows per workgroup slice and number of slices.
 constexpr int kAttnMaxSplits = 256;
 constexpr int64_t kAttnMaxLen = 262144;
-constexpr int64_t kAttnDirectWork = 65536;       // rows x heads x head_dim up to this: one slice, no merge
+constexpr int64_t kAttnDirectLen = 128;          // rows up to this, or rows x heads x head_dim
+constexpr int64_t kAttnDirectWork = 65536;       // up to this: one slice, no merge
 struct AttnPlan { int tc; int nsplit; };
 AttnPlan attn_decode_plan(int hkv, int group, int d, int64_t len, int cu_count);
 size_t attn_decode_workspace_bytes(int32_t hq, int32_t d);

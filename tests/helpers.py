@@ -60,6 +60,11 @@ def gemm_plan(m, n, k, cu=256):
     return _plan("_ZN2qm9gemm_planEllli", "llli", m, n, k, cu)
 
 
+def attn_decode_slices(hkv, group, d, length, cu=256):
+    """(rows per slice, slices) of decode attention."""
+    return _plan("_ZN2qm16attn_decode_planEiiili", "iiili", hkv, group, d, length, cu)[:2]
+
+
 def moe_few_rows(fmt, m, top_k, experts, hidden, inter, cu=256):
     """Whether the expert products of a call take the few-row kernel."""
     return _plan_fn("_ZN2qm12moe_few_rowsEilillli", "ilillli", ctypes.c_bool)(fmt, m, top_k, experts, hidden, inter, cu)

@@ -22,6 +22,7 @@ def test_one_slice_limit(d, group, edge):
 
 @pytest.mark.parametrize("hq,hkv,d,length", [
     (2, 2, 64, 1), (16, 2, 128, 15), (8, 2, 64, 31), (4, 2, 128, 65),     # fewer rows than a step
+    (48, 8, 128, 97), (64, 8, 128, 128), (64, 8, 128, 129),               # one slice up to 128 rows at any group
     (8, 4, 128, 64 * 128), (8, 4, 128, 64 * 128 + 1),                     # whole slices, then one row more
     (6, 2, 64, 256 * 64 + 3), (16, 2, 128, 40000),                        # the largest number of slices
 ])

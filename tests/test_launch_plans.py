@@ -4,7 +4,7 @@ needed)."""
 import pytest
 
 from paper_2607_00501_amd import binding as B
-from tests.helpers import fewrow_plan, fewrow_swiglu_plan, moe_few_rows
+from tests.helpers import attn_decode_slices, fewrow_plan, fewrow_swiglu_plan, moe_few_rows
 
 
 # The few-row kernel addresses activations in 16-byte units of 32 bits: the last
@@ -53,3 +53,13 @@ def test_fewrow_leaves_short_k_on_wide_matrices_to_the_tiles():
         for n in (16448, 151936):
             assert fewrow_plan(fmt, 16, n, 512) == (4, 4, 1) and fewrow_plan(fmt, 17, n, 992) is None
             assert fewrow_plan(fmt, 32, n, 1024) == (4, 8, 1) and fewrow_plan(fmt, 33, n, 1024) is None
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("group", range(1, 9))
+def test_decode_attention_of_short_caches_is_one_launch(d, group):
+    one = max(128, 65536 // (group * d))
+    for hkv in (1, 8, 128):
+        for length in (1, 64, 128, one):
+            assert attn_decode_slices(hkv, group, d, length) == (length, 1)
+        assert attn_decode_slices(hkv, group, d, one + 1)[1] > 1
