@@ -28,7 +28,7 @@ COMMON = [
 # overrides (for tuning sweeps only; the default build ignores them).
 if os.environ.get("QM_BUILD_TUNING") == "1":
     COMMON.append("-DQM_TUNING_OVERRIDES")
-SOURCES = ["api.cpp", "format.hip", "gemv.hip", "gemm.hip", "fewrow.hip", "moe.hip", "attention.hip", "decode.hip"]
+SOURCES = ["api.cpp", "format.hip", "gemv.hip", "gemm.hip", "gemm_swiglu.hip", "fewrow.hip", "moe.hip", "attention.hip", "decode.hip"]
 
 
 def _compile(src: str) -> str:
@@ -50,7 +50,7 @@ def build(verbose: bool = False) -> str:
     if shutil.which(HIPCC) is None and not os.path.exists(HIPCC):
         raise RuntimeError("hipcc not found; set HIPCC")
     os.makedirs(BUILD_DIR, exist_ok=True)
-    with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as ex:
+    with concurrent.futures.ThreadPoolExecutor(max_workers=min(9, os.cpu_count() or 1)) as ex:
         objs = list(ex.map(_compile, SOURCES))
     tmp = OUT + ".tmp"
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs

@@ -87,9 +87,16 @@ FewrowPlan fewrow_plan(int32_t fmt, int64_t m, int64_t n, int64_t k, int cu_coun
 // Every workgroup covers its rows of both matrices.  As in fewrow_plan, the
 // first tile whose grid fits one workgroup per CU (Q4 2048 -> 2 x 8192: m = 16
 // 9.3 -> 6.9 us against the grouped call and the elementwise kernel, 32 11.3 ->
-// 8.5; the MFMA tiles take 14.2 and 15.6); 32-row blocks also with two per CU
-// (m = 64: 14.8 -> 13.6, tiles 14.9), but not for Q8 and the float formats (Q8:
-// 18.6, tiles 17.2).
+// 8.5).  Wider matrices keep up to 16 rows on 16-row blocks (Q5 and Q6 with one
+// weight tile, their registers leave no room for two: 3584 -> 2 x 18944 at m = 8
+// Q6 25.6 vs 30.2) and up to 32 on 32-row blocks (there, Q4, us, few-row / two
+// calls / GEMM tile: m = 8 19.5 / 20.9 / 35.6, 32 27.5 / 32.3 / 36.5; Q8 27.7 /
+// 29.4 / 47.6, 38.9 / 42.3 / 48.6).  More rows: up to two 32-row blocks per CU
+// where the single-panel GEMM tiles do not run (4096 -> 2 x 3072 at m = 160 Q4 20.5,
+// 64 x 128 tile 23.4) or K is short (1024 -> 2 x 3072 at m = 96 Q4 8.0, tile 9.2; 2048
+// -> 2 x 5632 at m = 48, 1.4 per CU, 12.6 / 13.0, Q6 16.8 / 16.4; 2 per CU at 2048 ->
+// 2 x 8192 13.8 / 13.6 and 18.7 / 15.9), but not for Q8 and the float formats (2048 ->
+// 2 x 8192 Q8 17.8, tile 14.1).
 FewrowPlan fewrow_swiglu_plan(int32_t fmt, int64_t m, int64_t n, int64_t k, int cu_count) {
   if (!fewrow_addressable(m, k)) return FewrowPlan{0, 0, 1};
   const int64_t panels = padded_rows(n) / kPanel;
@@ -98,7 +105,13 @@ FewrowPlan fewrow_swiglu_plan(int32_t fmt, int64_t m, int64_t n, int64_t k, int 
   if (groups(RT, XR) <= cu_count) return FewrowPlan{RT, XR, 1};
   QM_FEWROW_SWIGLU_TILES(QM_FR)
 #undef QM_FR
-  if (groups(2, 8) <= 2 * cu_count && fmt_bits(fmt) < 8) return FewrowPlan{2, 8, 1};
+  const FewrowPlan wide = m > 16 ? FewrowPlan{2, 8, 1} : FewrowPlan{fmt == QM_Q5_G32 || fmt == QM_Q6_G32 ? 1 : 2, 4, 1};
+  const int64_t g = groups(wide.rt, wide.xr);
+  if (m <= 32 && fewrow_launchable(g)) return wide;
+  const bool pair_tile = 2 * panels * ((m + 63) / 64) <= cu_count;       // as launch_gemm_swiglu
+  if (m > 32 && fmt_bits(fmt) < 8 && g <= 2 * cu_count &&
+      (!pair_tile || k <= 1024 || (k <= 2048 && 2 * g <= 3 * cu_count)))
+    return wide;
   return FewrowPlan{0, 0, 1};
 }
 

@@ -138,56 +138,6 @@ hipError_t launch_args(const QgemmArgs& a, int32_t fmt, int cu_count, hipStream_
 
 }  // namespace
 
-namespace {
-
-template <int BM, int WN, int WK, int FMT>
-hipError_t launch_swiglu_tile(const QgemmArgs& a, hipStream_t st) {
-  const int64_t panels = padded_rows(a.N) / kPanel;
-  const dim3 grid(static_cast<unsigned>((panels + WN / 2 - 1) / (WN / 2)), static_cast<unsigned>((a.M + BM - 1) / BM));
-  hipLaunchKernelGGL((qgemm_kernel<BM, WN, WK, QgMode::kSwiglu, 2, false, FMT>), grid, dim3(WN * WK * 64), 0, st, a);
-  return hipGetLastError();
-}
-
-}  // namespace
-
-// Gate and up products with the SwiGLU in the epilogue: the tile of the two
-// matrices side by side (gemm_plan of 2n columns) from those with an even
-// number of column panels, 64 x 128 with 2-way split-K where it has none (the
-// single-panel tiles).  Measured against the grouped GEMM and the elementwise
-// kernel (Q4, us): 2048 -> 2 x 8192 at m = 512 50.4 -> 37.1, at 128 20.7 ->
-// 15.2; 1024 -> 2 x 3072 at m = 512 19.7 -> 13.8.  (4-way split-K in the place
-// of 2-way: within 5% either way below 128 rows.)
-hipError_t launch_gemm_swiglu(int32_t fmt, const uint8_t* qg, const uint16_t* sg, const uint8_t* qu,
-                              const uint16_t* su, const uint16_t* x, uint16_t* h, int64_t m, int64_t n, int64_t k,
-                              int cu_count, hipStream_t st) {
-  if (n == 0) return hipSuccess;
-  QgemmArgs a{};
-  a.a = x; a.M = m; a.K = k; a.N = n; a.h = h;
-  a.q = qg; a.s = sg; a.q2 = qu; a.s2 = su;
-  a.gq[0] = qg; a.gs[0] = sg; a.gq[1] = qu; a.gs[1] = su;
-  const FewrowPlan f = fewrow_swiglu_plan(fmt, m, n, k, cu_count);
-  if (f.rt != 0) return launch_fewrow_swiglu(a, fmt, f, st);
-  const GemmPlan p = gemm_plan(m, 2 * padded_rows(n), k, cu_count);
-  auto go = [&](auto ft) -> hipError_t {
-    constexpr int F = decltype(ft)::value;
-    if (p.bm == 128) return launch_swiglu_tile<128, 4, 1, F>(a, st);
-    if (p.bm == 64 && p.wn == 4 && p.wk == 2) return launch_swiglu_tile<64, 4, 2, F>(a, st);
-    if (p.bm == 64 && p.wn == 4) return launch_swiglu_tile<64, 4, 1, F>(a, st);
-    return launch_swiglu_tile<64, 2, 2, F>(a, st);
-  };
-  switch (fmt) {
-    case QM_Q4_G32: return go(std::integral_constant<int, QM_Q4_G32>{});
-    case QM_Q8_G32: return go(std::integral_constant<int, QM_Q8_G32>{});
-    case QM_Q2_G32: return go(std::integral_constant<int, QM_Q2_G32>{});
-    case QM_Q3_G32: return go(std::integral_constant<int, QM_Q3_G32>{});
-    case QM_Q5_G32: return go(std::integral_constant<int, QM_Q5_G32>{});
-    case QM_Q6_G32: return go(std::integral_constant<int, QM_Q6_G32>{});
-    case QM_F16: return go(std::integral_constant<int, QM_F16>{});
-    case QM_BF16: return go(std::integral_constant<int, QM_BF16>{});
-    default: return hipErrorInvalidValue;
-  }
-}
-
 bool gemm_plan_instantiated(const GemmPlan& p) {
 #define QM_HAS(BM, WN, WK) \
   if (p.bm == BM && p.wn == WN && p.wk == WK) return true;

@@ -46,7 +46,9 @@
 //    assignment slot); kSwiglu (dense rows; half of a workgroup's wavefronts
 //    take gate panels, the other half the up panels of the same columns, each
 //    on the full row tile as in kDense, and the epilogue swaps halves of the
-//    two blocks through LDS and writes fp16 silu(gate) * up).
+//    two blocks through LDS and writes fp16 silu(gate) * up; with one wavefront
+//    per K slice its 64 columns are 32 of the gate and the same 32 of the up
+//    matrix, which meet in its registers).
 //    MoE workgroups find their (expert, row tile) from the per-expert counts
 //    on the device, so no host synchronisation is needed.
 #pragma once
@@ -285,6 +287,22 @@ __device__ __forceinline__ uint32_t pair_halves(float a, float b, int lane) {
   return lane & 1 ? __builtin_amdgcn_perm(own, nb, 0x07060302u) : __builtin_amdgcn_perm(nb, own, 0x05040100u);
 }
 
+// Rows lr, lr + 1 of a SwiGLU tile's lane column: as dwords where pairs holds
+// (an even width and an aligned h, so that columns come in pairs), else one by one.
+__device__ __forceinline__ void store_h(uint16_t* h, int64_t n, int64_t row0, int lr, int rows, int64_t col,
+                                        const float (&hv)[2], bool pairs, int lane) {
+  if (pairs) {
+    const uint32_t v = pair_halves(hv[0], hv[1], lane);
+    if (lr + (lane & 1) < rows && col < n)
+      *reinterpret_cast<uint32_t*>(h + (row0 + lr + (lane & 1)) * n + (col & ~int64_t(1))) = v;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      if (lr + i < rows && col < n)
+        h[(row0 + lr + i) * n + col] = __builtin_bit_cast(uint16_t, static_cast<_Float16>(hv[i]));
+  }
+}
+
 // Wavefront 0 maps the workgroup's linear tile index to (expert, row tile)
 // in expert order, with ceil(count / BM) tiles per expert.  Expert -1 when
 // the index lies beyond the last tile.
@@ -333,6 +351,8 @@ struct Cfg {
   static constexpr int kPieces16 = kChunkBytes / 1024, kPieces4 = kChunkBytes % 1024 / 256;
   static constexpr bool kDual = MODE == QgMode::kMoeGateUp;
   static constexpr int kNB = kDual ? 2 : 1;                      // weight matrices per wavefront
+  // Column halves of a wavefront from two matrices (kSwiglu, one wavefront per slice).
+  static constexpr bool kPair = MODE == QgMode::kSwiglu && WN == 1;
   static constexpr int kThreads = WN * WK * 64;
   static constexpr int kSliceThreads = WN * 64;
   static constexpr int kTM = BM / 32;
@@ -366,10 +386,11 @@ struct Cfg {
   // Split-K partial sums of slices 1..WK-1, in halves (fp32 = 2 halves).
   static constexpr int kRedHalves = (WK - 1) * WN * kTM * 2 * kNB * 16 * 64 * 2;
   // kSwiglu: half of every wavefront's block of slice 0.
-  static constexpr int kSwapHalves = MODE == QgMode::kSwiglu ? WN * kTM * 16 * 64 * 2 : 0;
+  static constexpr int kSwapHalves = MODE == QgMode::kSwiglu && !kPair ? WN * kTM * 16 * 64 * 2 : 0;
   static constexpr int kLdsMax = kRedHalves > kSwapHalves ? kRedHalves : kSwapHalves;
   static constexpr int kLdsHalves = kAStages * kStageBytes / 2 > kLdsMax ? kAStages * kStageBytes / 2 : kLdsMax;
-  static_assert(MODE != QgMode::kSwiglu || (WN % 2 == 0 && kTM % 2 == 0), "kSwiglu pairs wavefronts and splits rows");
+  static_assert(MODE != QgMode::kSwiglu || kPair || (WN % 2 == 0 && kTM % 2 == 0),
+                "kSwiglu pairs wavefronts and splits rows, or pairs column halves");
   static_assert(kAStages == kSlots || (kAStages == 2 && DEPTH == 2), "A stage schedule");
 };
 
@@ -443,7 +464,14 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
     n_wave = static_cast<int64_t>(gp - first) * kPanel;
     cols_ok = gp < p.gpanel[p.gcount];
   }
-  if constexpr (MODE == QgMode::kSwiglu) {
+  if constexpr (C::kPair) {
+    // The halves of a panel share the lines of its scales: one XCD.
+    int64_t panel;
+    int half;
+    xcd_group_member(blockIdx.x, npad / kPanel, 2, &panel, &half);
+    n_wave = panel * kPanel + 32 * half;
+    cols_ok = true;
+  } else if constexpr (MODE == QgMode::kSwiglu) {
     const bool up = wn >= WN / 2;
     mq = up ? p.gq[1] : p.gq[0];
     ms = up ? p.gs[1] : p.gs[0];
@@ -487,11 +515,12 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
   // the lane part is a 32-bit offset.
   const int64_t panel = (cols_ok ? n_wave : mnpad - kPanel) / kPanel;
   const int64_t mat_q = npad / kPanel * G * CB, mat_s = npad * G;   // bytes / scales of one matrix (MoE)
-  const uint8_t* b_q[NB];
-  const uint16_t* b_s[NB];
+  const uint8_t* b_q[C::kPair ? 2 : NB];
+  const uint16_t* b_s[C::kPair ? 2 : NB];
+  const int half = C::kPair ? static_cast<int>(n_wave >> 5) & 1 : 0;
   b_q[0] = mq + expert * mat_q + panel * G * CB;
   b_s[0] = C::kFloat ? ms : ms + expert * mat_s + panel * G * kPanel;   // float weights: no scales (null)
-  if constexpr (NB == 2) {
+  if constexpr (NB == 2 || C::kPair) {
     b_q[1] = p.q2 + expert * mat_q + panel * G * CB;
     b_s[1] = C::kFloat ? p.s2 : p.s2 + expert * mat_s + panel * G * kPanel;
   }
@@ -555,27 +584,26 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         const int gc = min(2 * kt + c, G - 1);
-        const uint8_t* bq = b_q[j] + static_cast<int64_t>(gc) * CB;
-        if constexpr (C::kFloat) {
-          // Row 32h + l%32: quarter 2(l/32) + s holds its k = 16(l/32) + 8s .. + 7.
+        // Column half h: panel rows 32 hr + l%32 of matrix hj.
 #pragma unroll
-          for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < 2; ++h) {
+          const int hj = C::kPair ? h : j, hr = C::kPair ? half : h;
+          const uint8_t* bq = b_q[hj] + static_cast<int64_t>(gc) * CB;
+          if constexpr (C::kFloat) {
+            // Quarter 2(l/32) + s of the row holds its k = 16(l/32) + 8s .. + 7.
 #pragma unroll
             for (int sub = 0; sub < 2; ++sub) {
               const u32x4* qa = reinterpret_cast<const u32x4*>(bq + (2 * (lane >> 5) + sub) * 1024 +
-                                                               16 * (32 * h + (lane & 31)));
+                                                               16 * (32 * hr + (lane & 31)));
               rf[C::kFloat ? sl : 0][j][c][h][sub] = NT ? __builtin_nontemporal_load(qa) : *qa;
             }
-          continue;
-        }
-        const uint16_t* bs = b_s[j] + static_cast<int64_t>(gc) * kPanel;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const uint16_t* sa = bs + bs_lane + 32 * h;
+            continue;
+          }
+          const uint16_t* sa = b_s[hj] + static_cast<int64_t>(gc) * kPanel + bs_lane + 32 * hr;
           if constexpr (PL) {
-            // Row 32h + l%32, lane half l/32: the planes of the bit-plane
-            // formats (plain loads; these tiles are not built with NT).
-            const int row = 32 * h + (lane & 31), lh = lane >> 5;
+            // Lane half l/32: the planes of the bit-plane formats (plain
+            // loads; these tiles are not built with NT).
+            const int row = 32 * hr + (lane & 31), lh = lane >> 5;
             uint32_t* w = rw[sl][j][c][h];
             if constexpr (FMT == QM_Q5_G32 || FMT == QM_Q6_G32) {
               const u32x2 nb = *reinterpret_cast<const u32x2*>(bq + row * 16 + 8 * lh);
@@ -589,7 +617,7 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
             rs[sl][j][c][h] = *sa;
             continue;
           }
-          const BVec* qa = reinterpret_cast<const BVec*>(bq + bq_lane + h * 512);
+          const BVec* qa = reinterpret_cast<const BVec*>(bq + bq_lane + hr * 512);
           if constexpr (NT) {
             rb[sl][j][c][h] = __builtin_nontemporal_load(qa);
             rs[sl][j][c][h] = __builtin_nontemporal_load(sa);
@@ -856,7 +884,7 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
           for (int r = 0; r < 16; ++r) dst[((a * 2 * NB + b) * 16 + r) * 64 + lane] = acc[a][b][r];
     }
     __syncthreads();
-    if (MODE != QgMode::kSwiglu && wk > 0) return;
+    if ((MODE != QgMode::kSwiglu || C::kPair) && wk > 0) return;
 #pragma unroll 1
     for (int j = 1; j < (wk > 0 ? 0 : WK); ++j) {
       const float* src = red + ((j - 1) * WN + wn) * per_wave;
@@ -871,7 +899,20 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
 
   // Epilogue: lane l, register r of a 32x32 tile holds
   // row 8*(r/4) + 4*(l/32) + r%4, column l%32.
-  if constexpr (MODE == QgMode::kSwiglu) {
+  if constexpr (C::kPair) {
+    const bool pairs = mN % 2 == 0 && (reinterpret_cast<uintptr_t>(p.h) & 3u) == 0;
+    const int64_t col = n_wave + (lane & 31);
+#pragma unroll
+    for (int a = 0; a < C::kTM; ++a)
+#pragma unroll
+      for (int r = 0; r < 16; r += 2) {
+        float hv[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) hv[i] = silu_mul(acc[a][0][r + i], acc[a][1][r + i]);
+        store_h(p.h, mN, row0, a * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), rows, col, hv, pairs, lane);
+      }
+    return;
+  } else if constexpr (MODE == QgMode::kSwiglu) {
     // The gate wavefront of a column panel finishes the upper half of the row
     // tiles, its up wavefront the lower half: each hands the other half of its
     // block over in LDS (the A stages, or the split-K sums, are used up).
@@ -906,17 +947,8 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
             const float theirs = other[((a * 2 + b) * 16 + r + i) * 64];
             hv[i] = silu_mul(up ? theirs : mine, up ? mine : theirs);
           }
-          const int lr = (up ? TH + a : a) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-          if (pairs) {                                     // (columns come in pairs: n is even)
-            const uint32_t v = pair_halves(hv[0], hv[1], lane);
-            if (lr + (lane & 1) < rows && col < mN)
-              *reinterpret_cast<uint32_t*>(p.h + (row0 + lr + (lane & 1)) * mN + (col & ~int64_t(1))) = v;
-          } else {
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-              if (lr + i < rows && col < mN)
-                p.h[(row0 + lr + i) * mN + col] = __builtin_bit_cast(uint16_t, static_cast<_Float16>(hv[i]));
-          }
+          store_h(p.h, mN, row0, (up ? TH + a : a) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), rows, col, hv,
+                  pairs, lane);
         }
       }
     return;

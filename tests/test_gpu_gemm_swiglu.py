@@ -9,7 +9,7 @@ import torch
 from oracle import qmatmul_oracle as O
 from paper_2607_00501_amd import binding as B
 from paper_2607_00501_amd import inputs
-from tests.helpers import MFMA_TOL, rel_err
+from tests.helpers import MFMA_TOL, fewrow_swiglu_plan, gemm_plan, rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -57,6 +57,50 @@ def test_swiglu_gemm_parity(fmt, m, n, k):
                                          (300, 5002, 1), (590, 4999, 0)])
 def test_swiglu_gemm_odd_width_and_alignment(m, n, offset):
     _check(m, n, 64, (O.Q4, B.Q4_G32), offset)
+
+
+WIDE = [f for f in FORMATS if f[1] in (B.Q8_G32, B.F16, B.BF16)]
+
+
+@pytest.mark.parametrize("m,n,k,tile,fmt", [
+    (m, n, k, tile, f) for m, n, k, tile, fmts in [
+        (50, 8190, 2080, (64, 1, 4), FORMATS),      # 128 column blocks a matrix, K with a half last step
+        (50, 4101, 4128, (64, 1, 8), FORMATS),      # odd width, slices of unequal length
+        (70, 4000, 2080, (32, 1, 4), FORMATS),      # a last panel half filled
+        (300, 1000, 544, (32, 1, 2), WIDE),         # (the others are on the few-row kernel)
+        (300, 1000, 96, (32, 1, 1), WIDE),
+    ] for f in fmts])
+def test_swiglu_gemm_column_halves_sampled(m, n, k, tile, fmt):
+    """The single-panel tiles: 32 gate and 32 up columns per workgroup."""
+    panels = (n + 63) // 64
+    assert fewrow_swiglu_plan(fmt[1], m, n, k) is None and gemm_plan(m, 128 * panels, k) == tile
+    assert panels * ((m + 63) // 64) <= 128
+    ws = [inputs.weights_np(31 * m + i, (n, k), sigma=0.05) for i in (0, 1)]
+    x = inputs.activations_np(m + k, (m, k))
+    dev = [B.qm_repack(B.qm_quantise(torch.from_numpy(w).cuda(), fmt[1]), B.LAYOUT_DEVICE) for w in ws]
+    buf = torch.full((m * n + 8,), 9.0, dtype=torch.float16, device="cuda")
+    B.qmatmul_gemm_swiglu_f16(*dev, torch.from_numpy(x).cuda(), out=buf[2:2 + m * n].view(m, n))
+    y = buf[2:2 + m * n].view(m, n).cpu().numpy()
+    cols = np.unique(np.concatenate([np.random.default_rng(k).choice(n, 200, replace=False),
+                                     [0, 31, 32, 63, 64, n - 33, n - 1]]))
+    G, U = (O.gemm(O.pack(q, fmt[0]), s, fmt[0], x) for q, s in (O.quantise(w[cols], fmt[0]) for w in ws))
+    assert rel_err(y[:, cols], O.silu(G) * U) <= MFMA_TOL
+    assert (buf[:2] == 9.0).all() and (buf[2 + m * n:] == 9.0).all()
+
+
+@pytest.mark.parametrize("fmt", FORMATS, ids=lambda f: str(f[1]))
+@pytest.mark.parametrize("m", [13, 29])
+def test_swiglu_gemm_few_rows_of_a_wide_matrix_sampled(fmt, m):
+    """More sub-panels than two per CU: 16- and 32-row blocks all the same."""
+    n, k = 17000, 160
+    assert fewrow_swiglu_plan(fmt[1], m, n, k)[1] == (4 if m <= 16 else 8)
+    ws = [inputs.weights_np(41 * m + i, (n, k), sigma=0.05) for i in (0, 1)]
+    x = inputs.activations_np(m, (m, k))
+    dev = [B.qm_repack(B.qm_quantise(torch.from_numpy(w).cuda(), fmt[1]), B.LAYOUT_DEVICE) for w in ws]
+    y = B.qmatmul_gemm_swiglu_f16(*dev, torch.from_numpy(x).cuda()).cpu().numpy()
+    cols = np.unique(np.concatenate([np.random.default_rng(k).choice(n, 200, replace=False), [0, 63, 64, n - 1]]))
+    G, U = (O.gemm(O.pack(q, fmt[0]), s, fmt[0], x) for q, s in (O.quantise(w[cols], fmt[0]) for w in ws))
+    assert rel_err(y[:, cols], O.silu(G) * U) <= MFMA_TOL
 
 
 def test_swiglu_gemm_extreme_gates():

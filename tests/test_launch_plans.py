@@ -47,6 +47,14 @@ def test_fewrow_grids_can_be_launched():
     assert large((64 << 20) - 640, 1024) and not large(64 << 20, 1024)
 
 
+def test_fewrow_swiglu_grids_can_be_launched():
+    for m in (2, 16, 32):
+        assert fewrow_swiglu_plan(B.Q4_G32, m, 64 * ((1 << 22) - 1), 32) == (2, 4 if m <= 16 else 8, 1)
+        assert fewrow_swiglu_plan(B.Q4_G32, m, 64 << 22, 32) is None
+    assert fewrow_swiglu_plan(B.Q6_G32, 2, 64 * ((1 << 21) - 1), 32) == (1, 4, 1)
+    assert fewrow_swiglu_plan(B.Q6_G32, 2, 64 << 21, 32) is None
+
+
 def test_fewrow_leaves_short_k_on_wide_matrices_to_the_tiles():
     """More panels than CUs: up to 16 rows at any K, up to 32 from K = 1024."""
     for fmt in (B.Q4_G32, B.Q8_G32, B.F16):
