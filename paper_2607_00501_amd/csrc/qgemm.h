@@ -705,12 +705,12 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
   // One K step t: register slot / LDS stage sl = t % (DEPTH + 1) holds step
   // t's operands, the slots of steps t+1 .. t+DEPTH-1 are in flight, and the
   // slot of step t-1 is refilled with step t+DEPTH once every wavefront of
-  // the slice is past step t-1 (the barrier at the top of the step).  tail: the
-  // last step of the slice may lie past K or its second half may; those products
-  // are left out, as their clamped activations may be infinite.
-  auto step = [&](auto slot, int t, auto tail) __attribute__((always_inline)) {
+  // the slice is past step t-1 (the barrier at the top of the step).  last: the
+  // step may be the slice's last, which may lie past K, or its second half may;
+  // those products are left out, as their clamped activations may be infinite.
+  auto step = [&](auto slot, int t, auto tail, auto last) __attribute__((always_inline)) {
     constexpr int sl = decltype(slot)::value;
-    constexpr bool kTail = decltype(tail)::value;
+    constexpr bool kLast = decltype(last)::value;
     using Refill = std::integral_constant<int, (sl + DEPTH) % NS>;
     wait_a(t, tail);
     slice_sync();
@@ -802,7 +802,7 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
     __builtin_amdgcn_sched_barrier(0);
     load_b(Refill{}, t + DEPTH);                           // B, DEPTH steps ahead
     __builtin_amdgcn_sched_barrier(0);                               // keep the loads at the top
-    if (kTail && WK > 1 && t >= my_steps) return;
+    if (kLast && WK > 1 && t >= my_steps) return;
     const char* At = a_tile(a_stage(slot, t));
     // Software pipeline over the four 16-deep substeps: the A fragments and
     // the dequantised B fragments of substep ks+1 are produced while the
@@ -818,7 +818,7 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
     }
 #pragma unroll
     for (int ks = 0; ks < kBK / 16; ++ks) {
-      if (kTail && ks == 2 && 2 * (kt0 + t) + 1 >= G) break;
+      if (kLast && ks == 2 && 2 * (kt0 + t) + 1 >= G) break;
       const int cur = ks & 1, nxt = cur ^ 1;
       if (ks + 1 < kBK / 16) {
 #pragma unroll
@@ -854,14 +854,20 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
   }(std::make_integer_sequence<int, DEPTH>{});
   using Slots = std::make_integer_sequence<int, NS>;
   int t = 0;
-  for (; t + NS < KTs; t += NS) {
+  // Up to NS steps are left for after the loop, the last one always, so that the
+  // tests for it stay out of the loop (in every step they cost split-K shapes 3
+  // to 6%).  Float weights, 32 registers a step, would spill with NS steps in
+  // flight there (BF16 128 x 256 tiles, 512 x 2048 -> 16384: 48 -> 53 us): their
+  // loop may take the last step, in its last slot.
+  constexpr int kKept = C::kFloat ? 0 : 1;
+  for (; t + NS + kKept <= KTs; t += NS) {
     [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
-      (step(std::integral_constant<int, I>{}, t + I, std::false_type{}), ...);
+      (step(std::integral_constant<int, I>{}, t + I, std::false_type{}, std::bool_constant<kKept == 0 && I == NS - 1>{}),
+       ...);
     }(Slots{});
   }
-  // The last 1 .. NS steps.
   [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
-    ((t + I < KTs ? step(std::integral_constant<int, I>{}, t + I, std::true_type{}) : void()), ...);
+    ((t + I < KTs ? step(std::integral_constant<int, I>{}, t + I, std::true_type{}, std::true_type{}) : void()), ...);
   }(Slots{});
   // No LDS DMA may still be in flight when the LDS is reused or the
   // workgroup ends (the prefetches past the last step included).

@@ -12,6 +12,7 @@ import pytest
 from paper_2607_00501_amd import binding as B
 
 OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+READELF = "/opt/rocm/llvm/bin/llvm-readelf"
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 
 
@@ -78,3 +79,22 @@ def test_lds_dma_waits_for_fragment_reads(tmp_path):
             dma += 1
             assert pending is None, f"{kernel} {pending} | {ins}"
     assert dma > 0
+
+
+def test_matrix_and_attention_kernels_do_not_spill(tmp_path):
+    """No GEMM, few-row, expert or attention kernel keeps registers in scratch
+    memory (its loads would also count in the waits for the LDS DMA)."""
+    if not os.path.exists(B.LIB_PATH) or shutil.which(READELF) is None:
+        pytest.skip("library or llvm-readelf not there")
+    with open(B.LIB_PATH, "rb") as f:
+        data = f.read()
+    sizes = {}
+    for i, co in enumerate(_code_objects(data)):
+        path = tmp_path / f"{i}.co"
+        path.write_bytes(co)
+        notes = subprocess.run([READELF, "--notes", str(path)], capture_output=True, text=True, check=True).stdout
+        names = re.findall(r"^ +\.symbol: +(\S+)\.kd$", notes, re.M)
+        scratch = re.findall(r"\.private_segment_fixed_size: (\d+)", notes)
+        assert len(names) == len(scratch)
+        sizes.update((n, int(c)) for n, c in zip(names, scratch) if re.search("qgemm|fewrow|attn", n))
+    assert len(sizes) > 100 and not [n for n, s in sizes.items() if s]
