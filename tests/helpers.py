@@ -27,6 +27,11 @@ GEMV_TOL = 2e-3    # fp32 accumulation
 MFMA_TOL = 1e-2    # fp16 MFMA inputs
 
 
+# (oracle's, library's) ids of the eight weight formats.
+FORMATS = [(O.Q4, B.Q4_G32), (O.Q8, B.Q8_G32), (O.Q2, B.Q2_G32), (O.Q3, B.Q3_G32), (O.Q5, B.Q5_G32),
+           (O.Q6, B.Q6_G32), (O.F16, B.F16), (O.BF16, B.BF16)]
+
+
 class _Plan(ctypes.Structure):
     _fields_ = [("a", ctypes.c_int), ("b", ctypes.c_int), ("c", ctypes.c_int)]
 

@@ -29,9 +29,9 @@ def _ref(w, x, ofmt):
     return O.gemm(O.pack(q, ofmt), s, ofmt, x)
 
 
-# Every tile of the plan: 128 x 256 (2048 x 4096), 64 x 256, 64 x 128
-# split-K (500 x 3000 x 2080), one-panel split-K with 64 and 32 rows;
-# ragged M, N, K.
+# The few-row kernel (up to 300 x 200 and 33 x 1000), 64 x 256 tiles, 64 x 128
+# split-K (500 x 3000 x 2080), one-panel split-K with 64 rows (200 x 4096) and
+# 128 x 256 (2000 x 4100); ragged M, N, K.
 @pytest.mark.parametrize("ofmt,bfmt", FMTS)
 @pytest.mark.parametrize("m,n,k", [(2, 64, 32), (5, 65, 96), (127, 130, 160), (300, 200, 2048),
                                    (33, 1000, 8192), (2048, 2048, 96), (200, 4096, 4128),
@@ -71,7 +71,7 @@ def test_gemm_every_output_last_k_steps(ofmt, bfmt, m, n, k):
 def test_gemm_formats_integer_grid_exact(ofmt, bfmt, m, n, k):
     """Scale-1 integer weights over every code in [-qmax, qmax] (F16/BF16:
     integers in [-64, 64], exact in both) and small integer X: the fp32
-    result is exact (B through registers and LDS)."""
+    result is exact (few-row kernel, 32-row tiles)."""
     rng = np.random.default_rng(40 + ofmt)
     qm = O.QMAX.get(ofmt, 64)
     w = rng.integers(-qm, qm + 1, size=(n, k))

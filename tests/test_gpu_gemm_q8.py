@@ -23,8 +23,8 @@ def _ref(w, x):
     return O.gemm(O.pack(q, O.Q8), s, O.Q8, x)
 
 
-# Every Q8 tile: 64 x 256 (two shapes), 64 x 128 split-K, one-panel split-K
-# slices of 64 and 32 rows; ragged M, N and K (K = 32 * odd, 8224, 4128).
+# The few-row kernel (up to 300 x 200 and 70 x 640), 32-row tiles (513 x 384), the
+# 64 x 256 tile and 64-row one-panel slices; ragged M, N and K (K = 32 * odd, 8224, 4128).
 @pytest.mark.parametrize("m,n,k", [(2, 64, 32), (5, 65, 96), (127, 130, 160), (129, 64, 64),
                                    (64, 256, 1024), (300, 200, 2048), (513, 384, 256),
                                    (128, 512, 2048), (33, 1000, 8192), (2048, 2048, 96),
@@ -39,8 +39,8 @@ def test_gemm_q8_parity(m, n, k):
 
 
 def test_gemm_q8_large_ragged_sampled():
-    """2000 x 4100 x 96: the shape class where Q4 takes 128 x 256 tiles and
-    Q8 64 x 256; sampled rows and columns across tile boundaries."""
+    """2000 x 4100 x 96, 128 x 256 tiles; sampled rows and columns across tile
+    boundaries."""
     m, n, k = 2000, 4100, 96
     w = inputs.weights_np(inputs.seed_for(5, n, "up", 3), (n, k))
     x = inputs.activations_np(inputs.seed_for(5, m, "x", 3), (m, k))

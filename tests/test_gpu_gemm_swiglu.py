@@ -9,12 +9,9 @@ import torch
 from oracle import qmatmul_oracle as O
 from paper_2607_00501_amd import binding as B
 from paper_2607_00501_amd import inputs
-from tests.helpers import MFMA_TOL, fewrow_swiglu_plan, gemm_plan, rel_err
+from tests.helpers import FORMATS, MFMA_TOL, fewrow_swiglu_plan, gemm_plan, rel_err
 
 pytestmark = pytest.mark.gpu
-
-FORMATS = [(O.Q4, B.Q4_G32), (O.Q8, B.Q8_G32), (O.Q2, B.Q2_G32), (O.Q3, B.Q3_G32), (O.Q5, B.Q5_G32),
-           (O.Q6, B.Q6_G32), (O.F16, B.F16), (O.BF16, B.BF16)]
 
 
 def _weights(seed, n, k, fmt):

@@ -3,7 +3,7 @@ MFMA GEMM, the grouped GEMM and the MoE layer against the oracle, on
 sampled outputs.  The shapes are drawn log-uniformly (M up to 2,600, N up to
 9,000, K up to 8,320, groups of up to four matrices; MoE with up to 64
 experts, top-k up to 8, ragged hidden and inter sizes), so the cases land on
-every launch plan with ragged edges."""
+most launch plans with ragged edges."""
 
 import numpy as np
 import pytest
