@@ -901,9 +901,18 @@ qm_status qm_device_config(char* buf, size_t len) {
     used += std::snprintf(buf + used, len - used, " gemv_q4(%lld->%lld)=%s", static_cast<long long>(sh[0]),
                           static_cast<long long>(sh[1]), name);
   }
-  if (used >= 0 && static_cast<size_t>(used) < len)
-    std::snprintf(buf + used, len - used, " gemm_tile(m=512,n=2048)=%s moe_tile(rows/expert=8)=%s "
-                  "moe_tile(rows/expert=128)=%s", gemm_tile_name(512, 2048), moe_tile_name(8), moe_tile_name(128));
+  // Q4 products of a 2048 -> 2048 projection, then a Q4 expert layer of 128
+  // experts of 2048 -> 768, top-8.
+  for (const int64_t m : {8, 512}) {
+    if (used < 0 || static_cast<size_t>(used) >= len) break;
+    used += std::snprintf(buf + used, len - used, " gemm_tile(m=%lld,n=2048)=%s", static_cast<long long>(m),
+                          gemm_tile_name(QM_Q4_G32, m, 2048, 2048, d->cu_count));
+  }
+  for (const int64_t m : {1, 128, 2048}) {
+    if (used < 0 || static_cast<size_t>(used) >= len) break;
+    used += std::snprintf(buf + used, len - used, " moe_tile(m=%lld)=%s", static_cast<long long>(m),
+                          moe_tile_name(QM_Q4_G32, m, 8, 128, 2048, 768, d->cu_count));
+  }
   return QM_OK;
 }
 

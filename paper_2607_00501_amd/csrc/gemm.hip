@@ -71,9 +71,14 @@ GemmPlan gemm_plan(int64_t m, int64_t n, int64_t k, int cu_count) {
   return GemmPlan{32, 1, wk};
 }
 
-const char* gemm_tile_name(int64_t m, int64_t n) {
+const char* gemm_tile_name(int32_t fmt, int64_t m, int64_t n, int64_t k, int cu_count) {
   static thread_local char buf[64];
-  const GemmPlan p = gemm_plan(m, n, 2048, 256);
+  const FewrowPlan f = fewrow_plan(fmt, m, n, k, cu_count);
+  if (f.rt != 0) {
+    std::snprintf(buf, sizeof(buf), "few-row, %d rows x %d", 4 * f.xr, 16 * f.rt);
+    return buf;
+  }
+  const GemmPlan p = gemm_plan(m, n, k, cu_count);
   std::snprintf(buf, sizeof(buf), "BM%d x %d, %d-way split-K", p.bm, 64 * p.wn, p.wk);
   return buf;
 }

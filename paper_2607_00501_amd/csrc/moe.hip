@@ -514,10 +514,6 @@ size_t moe_workspace_bytes(int64_t m, int32_t top_k, int64_t hidden, int64_t int
   return h_bytes + yp_bytes;
 }
 
-const char* moe_tile_name(int64_t rows_per_expert) {
-  return rows_per_expert <= 24 ? "32-row bucket tiles x 4 panels" : "64-row bucket tiles x 4 panels";
-}
-
 hipError_t launch_route(const float* logits, int64_t m, int32_t e, int32_t k, int32_t* ids, float* w,
                         int32_t* counts, int32_t* offsets, int32_t* sorted_assign, hipStream_t st) {
   if (small_route(m, e, k)) {
@@ -572,6 +568,37 @@ bool moe_few_rows(int32_t fmt, int64_t m, int32_t top_k, int64_t n_experts, int6
          32 * per_2cu * cu_count + n_experts * (inter + hidden) / 32;
 }
 
+namespace {
+
+// few: the few-row kernel; else 32-row tiles up to 24 rows per expert (rpe), with
+// 2-panel blocks for gate/up and down where narrow_g and narrow_d say so.
+struct MoePlan { bool few, narrow_g, narrow_d; int64_t rpe; };
+
+MoePlan moe_plan(int32_t fmt, int64_t m, int32_t top_k, int64_t n_experts, int64_t hidden, int64_t inter,
+                 int cu_count) {
+  const int64_t used = std::min<int64_t>(n_experts, m * top_k);
+  auto blocks = [&](int64_t n) { return used * ((padded_rows(n) + 255) / 256); };
+  return MoePlan{moe_few_rows(fmt, m, top_k, n_experts, hidden, inter, cu_count), 2 * blocks(inter) <= cu_count,
+                 4 * blocks(hidden) <= 3 * cu_count, m * top_k / n_experts};
+}
+
+constexpr bool gate_up_32_rows(int32_t fmt) { return fmt == QM_Q5_G32 || fmt == QM_Q6_G32 || fmt == QM_Q8_G32; }
+
+}  // namespace
+
+const char* moe_tile_name(int32_t fmt, int64_t m, int32_t top_k, int64_t n_experts, int64_t hidden, int64_t inter,
+                          int cu_count) {
+  static thread_local char buf[64];
+  const MoePlan p = moe_plan(fmt, m, top_k, n_experts, hidden, inter, cu_count);
+  if (p.few)
+    std::snprintf(buf, sizeof(buf), "few-row, 8 rows x 32 and 64");
+  else if (p.rpe <= 24)
+    std::snprintf(buf, sizeof(buf), "32-row bucket tiles x %d and %d panels", p.narrow_g ? 2 : 4, p.narrow_d ? 2 : 4);
+  else
+    std::snprintf(buf, sizeof(buf), "%d- and 64-row bucket tiles x 4 panels", gate_up_32_rows(fmt) ? 32 : 64);
+  return buf;
+}
+
 hipError_t launch_moe(const MoeArgs& a, int cu_count, hipStream_t st) {
   // Tuning sweeps only: QM_MOE_PLAN="bm_gate_up,wk_gate_up,bm_down,wk_down,
   // depth_gate_up,depth_down,nontemporal".
@@ -613,12 +640,9 @@ hipError_t launch_moe(const MoeArgs& a, int cu_count, hipStream_t st) {
   // 128 of 1024 -> 256, top-8 (128 blocks, down 4-panel) Q4 32.1 / 27.9.  Narrow
   // gate/up at 160 blocks (32 of 2048 -> 1280): Q4 51.4 / 48.0 but Q8 62.0 / 65.7;
   // at 192 (64 of 2048 -> 768) Q4 52.9 / 54.9, Q8 65.3 / 73.7.
-  const int64_t rpe = a.m * a.top_k / a.n_experts;
-  const int64_t used = std::min<int64_t>(a.n_experts, a.m * a.top_k);
-  auto blocks = [&](int64_t n) { return used * ((padded_rows(n) + 255) / 256); };
-  const bool narrow_g = 2 * blocks(a.inter) <= cu_count, narrow_d = 4 * blocks(a.hidden) <= 3 * cu_count;
-  const bool few = moe_few_rows(a.format, a.m, a.top_k, a.n_experts, a.hidden, a.inter, cu_count);
-  auto plan = [&](auto f) -> hipError_t {
+  const auto [few, narrow_g, narrow_d, rpe] =
+      moe_plan(a.format, a.m, a.top_k, a.n_experts, a.hidden, a.inter, cu_count);
+  auto plan = [&, few = few, narrow_g = narrow_g, narrow_d = narrow_d, rpe = rpe](auto f) -> hipError_t {
     constexpr int F = decltype(f)::value;
     if (few) return launch_moe_fewrow<2, 4, 2, F>(a, st);
     if (rpe <= 24) {
@@ -627,7 +651,7 @@ hipError_t launch_moe(const MoeArgs& a, int cu_count, hipStream_t st) {
       if (narrow_d) return launch_moe_tiles<32, 1, 32, 2, 4, 2, 2, true, F, 2>(a, st);
       return launch_moe_tiles<32, 1, 32, 1, 4, 2, 2, true, F, 4>(a, st);
     }
-    if constexpr (F == QM_Q5_G32 || F == QM_Q6_G32 || F == QM_Q8_G32) {
+    if constexpr (gate_up_32_rows(F)) {
       return launch_moe_tiles<32, 1, 64, 1, 4, 2, 2, false, F>(a, st);
     } else {
       if (rpe <= 64) return launch_moe_tiles<64, 1, 64, 1, 4, 2, 2, true, F>(a, st);

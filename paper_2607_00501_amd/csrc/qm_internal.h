@@ -266,7 +266,9 @@ constexpr bool fewrow_launchable(int64_t groups) { return groups < int64_t(1) <<
 // Whether the expert products of a call take the few-row kernel.
 bool moe_few_rows(int32_t fmt, int64_t m, int32_t top_k, int64_t n_experts, int64_t hidden, int64_t inter,
                   int cu_count);
-const char* gemm_tile_name(int64_t m, int64_t n);
-const char* moe_tile_name(int64_t rows_per_expert);
+// Tiles of a dense and of an expert-layer call, in words (thread-local text).
+const char* gemm_tile_name(int32_t fmt, int64_t m, int64_t n, int64_t k, int cu_count);
+const char* moe_tile_name(int32_t fmt, int64_t m, int32_t top_k, int64_t n_experts, int64_t hidden, int64_t inter,
+                          int cu_count);
 
 }  // namespace qm

@@ -75,6 +75,15 @@ def moe_few_rows(fmt, m, top_k, experts, hidden, inter, cu=256):
     return _plan_fn("_ZN2qm12moe_few_rowsEilillli", "ilillli", ctypes.c_bool)(fmt, m, top_k, experts, hidden, inter, cu)
 
 
+def gemm_tile_name(fmt, m, n, k, cu=256):
+    return _plan_fn("_ZN2qm14gemm_tile_nameEillli", "illli", ctypes.c_char_p)(fmt, m, n, k, cu).decode()
+
+
+def moe_tile_name(fmt, m, top_k, experts, hidden, inter, cu=256):
+    return _plan_fn("_ZN2qm13moe_tile_nameEilillli", "ilillli", ctypes.c_char_p)(
+        fmt, m, top_k, experts, hidden, inter, cu).decode()
+
+
 def _nibble_plane(u):
     """u [p, g, 64, 32] (values < 16) -> bytes [p, g, 64*16]: dword j of a
     row covers k = 8j..8j+7, nibble t holds k-offset 2t (t < 4) or

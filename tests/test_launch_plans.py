@@ -4,7 +4,8 @@ needed)."""
 import pytest
 
 from paper_2607_00501_amd import binding as B
-from tests.helpers import attn_decode_slices, fewrow_plan, fewrow_swiglu_plan, moe_few_rows
+from tests.helpers import (attn_decode_slices, fewrow_plan, fewrow_swiglu_plan, gemm_tile_name, moe_few_rows,
+                           moe_tile_name)
 
 
 # The few-row kernel addresses activations in 16-byte units of 32 bits: the last
@@ -71,3 +72,15 @@ def test_decode_attention_of_short_caches_is_one_launch(d, group):
         for length in (1, 64, 128, one):
             assert attn_decode_slices(hkv, group, d, length) == (length, 1)
         assert attn_decode_slices(hkv, group, d, one + 1)[1] > 1
+
+
+def test_tile_names_follow_the_plans():
+    assert gemm_tile_name(B.Q4_G32, 8, 2048, 2048) == "few-row, 8 rows x 16"
+    assert gemm_tile_name(B.Q4_G32, 512, 2048, 2048) == "BM64 x 64, 4-way split-K"
+    assert gemm_tile_name(B.Q8_G32, 2048, 2048, 8192) == "BM64 x 256, 2-way split-K"
+    layer = lambda fmt, m, experts=128: moe_tile_name(fmt, m, 8, experts, 2048, 768)
+    assert layer(B.Q4_G32, 1) == "few-row, 8 rows x 32 and 64"
+    assert layer(B.Q4_G32, 128) == "32-row bucket tiles x 4 and 4 panels"
+    assert moe_tile_name(B.Q4_G32, 48, 4, 32, 1024, 512) == "32-row bucket tiles x 2 and 2 panels"
+    assert layer(B.Q4_G32, 2048) == "64- and 64-row bucket tiles x 4 panels"
+    assert layer(B.Q8_G32, 2048) == "32- and 64-row bucket tiles x 4 panels"
