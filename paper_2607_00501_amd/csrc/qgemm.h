@@ -98,6 +98,14 @@ namespace qg {
 constexpr int kBK = 64;                 // K per step (two quantisation groups)
 constexpr int kMoeChunkTiles = 4;       // MoE row tiles per XCD chunk
 
+// First activation column of K step `step`, in 32 bits up to K = 2^31 - 32: steps
+// past the last one, which load but are not used, read the last one again.
+__host__ __device__ constexpr int step_column(int step, int steps) {
+  return (step < steps - 1 ? step : steps - 1) * kBK;
+}
+static_assert(step_column(3, 4) == 192 && step_column(6, 4) == 192 && step_column(0, 1) == 0);
+static_assert(step_column((1 << 25) + 2, 1 << 25) + 56 <= INT32_MAX - 7);
+
 // s_waitcnt vmcnt(N) with expcnt and lgkmcnt left free (gfx9 encoding:
 // vmcnt[3:0] in bits 3:0 and vmcnt[5:4] in bits 15:14).
 template <int N>
@@ -544,11 +552,11 @@ __device__ __forceinline__ void qgemm_body(const QgemmArgs& p) {
     return lds_b + st * C::kStageBytes + C::kAStageBytes + wave * C::kBWaveBytes;
   };
   auto load_a = [&](int st, int step) __attribute__((always_inline)) {
-    const int kt = kt0 + step;
+    const int k0 = step_column(kt0 + step, KT);
     char* tile = a_tile(st);
 #pragma unroll
     for (int i = 0; i < C::kALoads; ++i) {
-      const int k = min(kt * kBK + a_col[i], static_cast<int>(K) - 8);
+      const int k = min(k0 + a_col[i], static_cast<int>(K) - 8);
       lds_dma16(a_src[i] + k, tile + (i * WN + wn) * 1024);
     }
   };
