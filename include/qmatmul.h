@@ -322,10 +322,10 @@ qm_status qmatmul_gemm_grouped(int32_t count, const qm_qweight* w, const uint16_
 /* The gate and up projections of a prompt chunk with the SwiGLU as their
  * epilogue (Sec. 3.3: each fusion removes a launch and a round trip; Sec. 3.4):
  * h[m][n] = fp16_RNE(silu(G) * U), G and U the fp32 products of qmatmul_gemm
- * (their split-K partition may differ).  w_gate, w_up: one format (any of the
- * eight), one shape [n][k], DEVICE layout, batch 1.  X: fp16 [m][k] (16-byte
- * aligned); h: fp16 [m][n] (2-byte aligned), not overlapping X.
- * 1 <= m <= 65536 (m == 1 runs the GEMV of qmatmul_gemv_swiglu_f16).
+ * (their split-K partition may differ), silu(G) * U in fp32 to 2.5 ulp of 2^-23.
+ * w_gate, w_up: one format (any of the eight), one shape [n][k], DEVICE layout,
+ * batch 1.  X: fp16 [m][k] (16-byte aligned); h: fp16 [m][n] (2-byte aligned),
+ * not overlapping X.  1 <= m <= 65536 (m == 1 runs the GEMV of qmatmul_gemv_swiglu_f16).
  * Deterministic. */
 qm_status qmatmul_gemm_swiglu_f16(const qm_qweight* w_gate, const qm_qweight* w_up, const uint16_t* x, int64_t m,
                                   uint16_t* h, void* stream);
